@@ -62,9 +62,12 @@ int dense_proj_forward(const int8_t *Q, const float *scale, int32_t K, int32_t M
                        float *y, void *stream);
 
 /* Kernels: DENSE_KERNEL_REGISTER keeps each lane's slice of the activations
- * in registers (16-byte aligned Q, K % 16 == 0, K <= 4096, up to 4 batch
- * rows per launch); DENSE_KERNEL_STAGED stages them in LDS (any K, alignment,
- * up to 8 rows per launch).  The choice depends on K and Q's alignment only. */
+ * in registers (16-byte aligned Q, K % 16 == 0, K <= 4096): a vector form of
+ * up to 4 batch rows per launch and, for batches of more than 8 rows, or of
+ * more than 2 where M >= 1024, a matrix-core form that takes all rows in one
+ * launch with the same FMAs in the same order (identical bits).
+ * DENSE_KERNEL_STAGED stages the activations in LDS (any K, alignment, up to
+ * 8 rows per launch).  The choice depends on K and Q's alignment only. */
 #define DENSE_KERNEL_STAGED 1
 #define DENSE_KERNEL_REGISTER 2
 
@@ -79,7 +82,8 @@ int dense_proj_plan(int32_t K, int32_t M, int32_t B, int32_t q_align, int32_t *k
  * automatic choice.  DENSE_TUNE_KERNEL forces a kernel (the register kernel
  * only where it applies; results differ between the two kernels in the last
  * bits, each within the bound above).  DENSE_TUNE_WG_PER_CU caps the
- * register kernel's grid at value * 256 workgroups (results unchanged). */
+ * register kernel's grid at value * 256 workgroups and keeps it to its vector
+ * form (results unchanged). */
 #define DENSE_TUNE_KERNEL 1
 #define DENSE_TUNE_WG_PER_CU 2
 int dense_proj_tune(int32_t key, int32_t value);

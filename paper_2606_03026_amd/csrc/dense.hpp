@@ -386,4 +386,199 @@ __global__ __launch_bounds__(kRegBlock) void k_dense_reg(const int8_t* __restric
     }
 }
 
+// ---------------------------------------------------------------------------
+// Matrix-core form of the register kernel, for batches (same K and alignment
+// rule, bit-identical results).
+//
+// v_mfma_f32_16x16x1 with four blocks does, per block, one FP32 fused
+// multiply-add per output of a 16 x 16 tile (checked on the device against
+// fmaf, bit for bit, over normal, subnormal, huge, infinite and NaN inputs).
+// A block is one of the register kernel's 32 lane chains: chain l of a row
+// is fed its chunks l + 32 j in order, byte after byte, so every output goes
+// through the very same sequence of FMAs; the chains are then added in the
+// order of group32_sum's tree.
+//
+// Work split.  A workgroup of 8 waves owns 16 NB batch rows and walks row
+// steps of 16 RT weight rows; wave w runs chains 4 w .. 4 w + 3 (four
+// adjacent 16-byte chunks of a row: 64 contiguous bytes), so it keeps its
+// slice of the activations, 16 NPL NB floats per lane, in registers for the
+// whole launch, as the register kernel does, and reads only weights in the
+// loop.  Lane 16 i + c holds block i: row c of the weights, batch row c of
+// the activations.  The four chains of a wave are added in registers, the
+// eight waves' sums through LDS (double buffered: one barrier per row step,
+// met while the next step's products are under way).
+// It is bound by the FP32 matrix rate (RT NB independent accumulators keep
+// the pipe full; the byte conversions run in its shadow): 131-134 TFLOP/s for
+// this instruction alone, at the 2.15 GHz the chip then holds.  Measured, in
+// batches of cold weights, against launches of 2 rows each: 1536 -> 57344 at
+// 64 rows 100 us (113 TFLOP/s) against 497, 1536 -> 6144 at 500 rows 87 us
+// against 1427, 4096 -> 4096 at 200 rows 86 us against 1202.  Without the
+// raised priority of half the waves (the two waves of a SIMD then reach their
+// sums together and leave the pipe idle) and the bank-spreading pitch the
+// first two take 106 and 92 us, without the barrier moved into the next step
+// 104 and 90.
+// ---------------------------------------------------------------------------
+constexpr int kMatWaves = 8;
+constexpr int kMatBlock = 64 * kMatWaves;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int NPL, int NB, int RT>
+__global__ __launch_bounds__(kMatBlock) void k_dense_mat(const int8_t* __restrict__ Q, const float* __restrict__ scale,
+                                                         int K, int M, const float* __restrict__ x, int B,
+                                                         float* __restrict__ y, int row_wgs)
+{
+    constexpr int kRows = 16 * RT;        // weight rows of a step
+    constexpr int kOut = RT * NB * 256;   // outputs of a step
+    constexpr int kPer = (kOut + kMatBlock - 1) / kMatBlock;
+    // batch rows of a step's sums are kPitch floats apart: the 16 rows that a
+    // wave writes at once fall in distinct banks
+    constexpr int kPitch = kRows + 4;
+    __shared__ __align__(16) float part[2][kMatWaves][16 * NB * kPitch];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int blk = (threadIdx.x % 64) / 16, c = threadIdx.x % 16;
+    const int b0 = (blockIdx.x / row_wgs) * (16 * NB);
+    const int n_steps = (M + kRows - 1) / kRows;
+    const int n_chunks = K / 16;
+    const __amdgpu_buffer_rsrc_t qres = weight_resource(Q, (int64_t)M * K);
+    const __amdgpu_buffer_rsrc_t xres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, B * K * 4, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t sres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(scale), 0, M * 4, kBufferFlags);
+
+    // byte offset within a row of each chunk of this lane's chain (past the
+    // row: out of range, zero weights and zero activations)
+    uint32_t chunk_off[NPL];
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        const int ch = 4 * wave + blk + kRegLanes * j;
+        chunk_off[j] = ch < n_chunks ? (uint32_t)(ch * 16) : kOutOfRange;
+    }
+    u32x4 slot[RT][NPL];
+    auto load_tile = [&](int s, int rt, int j) {
+        const int m = s * kRows + 16 * rt + c;
+        const uint32_t off = m < M && chunk_off[j] != kOutOfRange ? (uint32_t)m * (uint32_t)K + chunk_off[j] : kOutOfRange;
+        slot[rt][j] = __builtin_amdgcn_raw_buffer_load_b128(qres, off, 0, 0);
+    };
+    int s = blockIdx.x % row_wgs;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < NPL; ++j)
+            load_tile(s, rt, j);
+
+    float xr[NB][NPL][16];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int b = b0 + 16 * nb + c;
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+            const bool ok = b < B && chunk_off[j] != kOutOfRange;
+            const uint32_t base = ok ? ((uint32_t)b * (uint32_t)K + chunk_off[j]) * 4u : kOutOfRange;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, base + 16 * t, 0, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    xr[nb][j][4 * t + e] = v[e];
+            }
+        }
+    }
+    // The eight waves' sums of step ps, from buffer `buf`: entry e =
+    // threadIdx.x + 512 i is batch row e / kRows, weight row e % kRows.
+    auto finish = [&](int ps, int buf, const float (&sc)[kPer]) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = threadIdx.x + kMatBlock * i;
+            if (kOut % kMatBlock != 0 && e >= kOut)
+                break;
+            float p[kMatWaves];
+#pragma unroll
+            for (int w = 0; w < kMatWaves; ++w)
+                p[w] = part[buf][w][e / kRows * kPitch + e % kRows];
+            const float tot = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            const int b = b0 + e / kRows, m = ps * kRows + e % kRows;
+            if (b < B && m < M)
+                y[(int64_t)b * M + m] = tot * sc[i];
+        }
+    };
+    // scales of a step's outputs, asked for a step before they are used
+    auto load_scales = [&](int ps, float (&sc)[kPer]) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int m = ps * kRows + (threadIdx.x + kMatBlock * i) % kRows;
+            sc[i] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(sres, m < M ? (uint32_t)m * 4u : kOutOfRange, 0, 0));
+        }
+    };
+    if (wave < 4)
+        __builtin_amdgcn_s_setprio(1);
+    float sc[kPer];
+    int buf = 0, done = -1;  // done: the step whose sums are in part[buf ^ 1], -1 before the first
+    for (; s < n_steps; s += row_wgs, buf ^= 1) {
+        f32x16 acc[RT][NB];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    acc[rt][nb][i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                // Early in a step the sums of the step before are finished: the
+                // waves meet while each has products of this step behind and
+                // ahead of it, so the matrix pipe does not drain at the barrier.
+                if (4 * j + i == 2 * NPL) {
+                    if (done >= 0) {
+                        __syncthreads();
+                        finish(done, buf ^ 1, sc);
+                    }
+                    load_scales(s, sc);
+                }
+                float w[RT][4];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const uint32_t d = slot[rt][j][i];
+                    // not cvt_i8: a matrix instruction must not follow the write of
+                    // its operand at once, and the compiler keeps that distance
+                    // only for instructions it knows
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        w[rt][t] = (float)(int32_t)(int8_t)(d >> (8 * t));
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            acc[rt][nb] = __builtin_amdgcn_mfma_f32_16x16x1f32(w[rt][t], xr[nb][j][4 * i + t],
+                                                                              acc[rt][nb], 0, 0, 0);
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)  // the next step's weights, a whole step ahead
+                load_tile(s + row_wgs, rt, j);
+        }
+        // register 4 i + r of lane 16 q + c: block i, weight row 4 q + r, batch row c
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                f32x4 v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    v[r] = (acc[rt][nb][r] + acc[rt][nb][4 + r]) + (acc[rt][nb][8 + r] + acc[rt][nb][12 + r]);
+                // This buffer was read two steps ago: every wave has passed the
+                // barrier of this step since, which it reaches with that done.
+                *reinterpret_cast<f32x4*>(&part[buf][wave][(16 * nb + c) * kPitch + 16 * rt + 4 * blk]) = v;
+            }
+        done = s;
+    }
+    __syncthreads();
+    if (done >= 0)
+        finish(done, buf ^ 1, sc);
+}
+
 }  // namespace spk

@@ -84,6 +84,44 @@ RegFn reg_fn(int npl, int bc)
     }
 }
 
+// Matrix-core form of the register kernel: NB 16-row batch tiles and RT 16-row
+// weight tiles per workgroup.  The activations (16 NPL NB), accumulators
+// (16 RT NB) and weights in flight (4 RT NPL) of a lane stay within the 256
+// registers that two waves per SIMD leave.
+using MatFn = void (*)(const int8_t*, const float*, int, int, const float*, int, float*, int);
+constexpr int mat_max_nb(int npl) { return npl <= 4 ? 2 : 1; }
+constexpr int mat_max_rt(int npl, int nb) { return 16 * npl * nb + 32 * nb + 8 * npl <= 200 ? 2 : 1; }
+
+template <int NPL>
+MatFn mat_fn_npl(int nb, int rt)
+{
+    if constexpr (mat_max_nb(NPL) >= 2)
+        if (nb == 2) {
+            if constexpr (mat_max_rt(NPL, 2) >= 2)
+                if (rt == 2)
+                    return spk::k_dense_mat<NPL, 2, 2>;
+            return spk::k_dense_mat<NPL, 2, 1>;
+        }
+    if constexpr (mat_max_rt(NPL, 1) >= 2)
+        if (rt == 2)
+            return spk::k_dense_mat<NPL, 1, 2>;
+    return spk::k_dense_mat<NPL, 1, 1>;
+}
+
+MatFn mat_fn(int npl, int nb, int rt)
+{
+    switch (npl) {
+    case 1: return mat_fn_npl<1>(nb, rt);
+    case 2: return mat_fn_npl<2>(nb, rt);
+    case 3: return mat_fn_npl<3>(nb, rt);
+    case 4: return mat_fn_npl<4>(nb, rt);
+    case 5: return mat_fn_npl<5>(nb, rt);
+    case 6: return mat_fn_npl<6>(nb, rt);
+    case 7: return mat_fn_npl<7>(nb, rt);
+    default: return mat_fn_npl<8>(nb, rt);
+    }
+}
+
 // Workgroups of a register kernel one CU holds at once (its VGPR use sets
 // it), asked of the runtime once per kernel; 2 while the query fails (no
 // device), without caching that.
@@ -116,6 +154,8 @@ struct DensePlan {
     int bc;        // batch rows per launch
     int npl;       // register kernel: 16-byte chunks per lane and row
     int rpg;       // rows per lane group (register kernel: the most any group takes)
+    int nb, rt;    // matrix-core form (nb > 0): 16-row batch and weight tiles per workgroup
+    int row_wgs;   // matrix-core form: workgroups that share the row steps of one batch tile
     int64_t wgs;   // workgroups per launch
     size_t lds;    // dynamic LDS bytes
 };
@@ -134,6 +174,35 @@ DensePlan make_plan(int32_t K, int32_t M, int32_t B, int q_align)
     const int tk = g_tune_kernel.load();
     p.kernel = (tk == DENSE_KERNEL_STAGED || !reg_ok) ? DENSE_KERNEL_STAGED : DENSE_KERNEL_REGISTER;
     const int wpc = g_tune_wg_per_cu.load();
+    // The matrix-core form gives the register kernel's bits, so batches move
+    // to it freely.  The vector form reads all of Q once per 1, 2 or 4 rows;
+    // one such launch beats a matrix-core one only up to its own row count
+    // (1536 -> 57344: 2 rows 17 us, 3 rows 31 us against 29, 13 rows 114
+    // against 31; 1536 -> 6144: 3 rows 11.7 against 8.3, 16 rows 46 against
+    // 9.9), and below 1024 rows of Q the matrix-core form has too few row
+    // steps to be worth it before 8 rows (1536 -> 300: 9 rows 20.6 against
+    // 8.3).  (A set DENSE_TUNE_WG_PER_CU asks for the vector form's grid.)
+    if (p.kernel == DENSE_KERNEL_REGISTER && wpc == 0 && (B > 8 || (B > 2 && M >= 1024))) {
+        p.npl = npl;
+        p.nb = B > 16 ? mat_max_nb(npl) : 1;
+        const int64_t b_tiles = (B + 16 * p.nb - 1) / (16 * p.nb);
+        p.rt = mat_max_rt(npl, p.nb);
+        if ((M + 31) / 32 * b_tiles < kCUs)
+            p.rt = 1;
+        const int64_t steps = (M + 16 * p.rt - 1) / (16 * p.rt);
+        // as many workgroups as the registers let run at once, shared out
+        // evenly over the batch tiles, a multiple of 8 each so that the
+        // workgroups of one row step sit on one XCD and share its L2
+        const int64_t resident = kCUs * (p.nb == 1 && npl <= 3 ? 2 : 1);
+        int64_t rw = std::min<int64_t>(steps, std::max<int64_t>(1, resident / b_tiles));
+        if (rw >= 8)
+            rw = rw / 8 * 8;
+        p.row_wgs = (int)rw;
+        p.bc = (int)std::min<int64_t>(b_tiles * 16 * p.nb, 1 << 30);
+        p.wgs = b_tiles * rw;
+        p.rpg = (int)((steps + rw - 1) / rw * p.rt);
+        return p;
+    }
     if (p.kernel == DENSE_KERNEL_REGISTER) {
         p.npl = npl;
         p.bc = 1;
@@ -260,7 +329,10 @@ int dense_proj_forward(const int8_t* Q, const float* scale, int32_t K, int32_t M
         const int32_t nb = std::min<int32_t>(p.bc, B - b0);
         const float* xb = x + (int64_t)b0 * K;
         float* yb = y + (int64_t)b0 * M;
-        if (p.kernel == DENSE_KERNEL_REGISTER)
+        if (p.nb > 0)
+            hipLaunchKernelGGL(mat_fn(p.npl, p.nb, p.rt), dim3((unsigned)p.wgs), dim3(spk::kMatBlock), 0, st, Q, scale,
+                               K, M, xb, nb, yb, p.row_wgs);
+        else if (p.kernel == DENSE_KERNEL_REGISTER)
             hipLaunchKernelGGL(reg_fn(p.npl, p.bc), dim3((unsigned)p.wgs), dim3(spk::kRegBlock), 0, st, Q, scale, K,
                                M, xb, nb, yb);
         else

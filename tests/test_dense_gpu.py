@@ -258,3 +258,37 @@ def test_dense_register_kernel_grid_does_not_change_results(sp, forced_kernel):
     np.testing.assert_array_equal(bits32(outs[0]), bits32(outs[1]))
     np.testing.assert_array_equal(bits32(outs[0]), bits32(outs[2]))
     assert_within_bound(outs[0], p["Q"], p["scale"], p["x"])
+
+
+# K for the chunk counts per lane of every matrix-core instantiation, with
+# ragged tails; M around the 16- and 32-row steps and past one step per
+# workgroup; B around the 16- and 32-row batch tiles.
+@pytest.mark.parametrize("K", [16, 80, 512, 528, 1024, 1536, 2048, 2560, 3072, 3584, 4096])
+@pytest.mark.parametrize("M,B", [(1, 9), (31, 16), (33, 17), (1031, 3), (2050, 33), (9001, 50)])
+def test_dense_matrix_core_batches_match_vector_form(sp, forced_kernel, K, M, B):
+    """The matrix-core form of the register kernel (batches) runs the same
+    FMAs in the same order as the vector form (forced by a grid cap): equal
+    bits, also for subnormal, huge, infinite and NaN activations; rows past B
+    keep their contents."""
+    p = wl.dense_problem(M, K, B, seed=10)
+    x = p["x"]
+    x[0, :] *= np.float32(2.0 ** -140)
+    x[1, ::3] *= np.float32(2.0 ** 118)
+    x[2, K // 2] = np.inf
+    x[B - 1, K - 1] = np.nan
+    assert sp.dense_proj_plan(K, M, B)["rows_per_launch"] >= B
+    Qd, sd = q_at(p["Q"], 0), dev(p["scale"])
+    xd = dev(np.concatenate([[np.float32(0)], x.ravel()]))[1:].view(B, K)  # 4-byte aligned only
+    y = torch.full((B + 1, M), 3.5, dtype=torch.float32, device="cuda")
+    sp.dense_proj_forward(Qd, sd, xd, B, y)
+    torch.cuda.synchronize()
+    forced_kernel(sp.DENSE_KERNEL_REGISTER, 2)
+    ref = torch.empty((B, M), dtype=torch.float32, device="cuda")
+    sp.dense_proj_forward(Qd, sd, xd, B, ref)
+    torch.cuda.synchronize()
+    got, ref = y.cpu().numpy(), ref.cpu().numpy()
+    assert (got[B:] == 3.5).all()
+    same = (bits32(got[:B]) == bits32(ref)) | (np.isnan(got[:B]) & np.isnan(ref))
+    assert same.all(), f"{int((~same).sum())} outputs differ, first at {np.argwhere(~same)[0]}"
+    if B > 4:
+        assert_within_bound(got[3:B - 1], p["Q"], p["scale"], x[3:B - 1])
