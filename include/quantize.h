@@ -26,8 +26,8 @@
  * paper withdraws (App. "Pure-INT4 Export Correction": scales taken after
  * transposing to [K][M]) cannot arise here.
  *
- * Sizes: 1 <= M, K <= 2^24 and M * K <= 2^31.  The call enqueues two kernels
- * on `stream` (a hipStream_t, NULL for the default stream) and returns; it
+ * Sizes: 1 <= M, K <= 2^24 and M * K <= 2^31.  The call enqueues one or two
+ * kernels on `stream` (a hipStream_t, NULL for the default stream) and returns; it
  * allocates nothing.  Q and scale must not overlap W.
  *
  * Errors: SPIKE_OK (0) or a negative code from spike_proj.h, with the

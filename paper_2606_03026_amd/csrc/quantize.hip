@@ -68,7 +68,30 @@ int spike_quantize_int8(const float* W, int32_t M, int32_t K, int32_t layout, in
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? SPIKE_OK : hip_fail(e, "quantizer launch");
     }
-    if (K % 4 == 0 && aligned(W, 16))
+    // Column-major in one pass: W moves once instead of twice, but only M / 16
+    // workgroups read it, and one CU takes in about 36 GB/s.  Short rows pay from
+    // 1024 rows on (1536 x 1536: 8.4 us against 11.2), longer ones only where
+    // about half the CUs have a workgroup (2048 x 4096: 14.1 against 15.7; 1536 x 6144:
+    // 17.4 against 16.9; 400 x 6000: 14.5 against 11.1).
+    if (layout == SPIKE_LAYOUT_COL_MAJOR && K % 4 == 0 && M % spk::kColRows == 0 && aligned(W, 16) &&
+        aligned(Q, 16) && ((K <= 2048 && M >= 1024) || (K <= spk::kQuantRowsMaxK && M >= 2048))) {
+        const int nv = (K + 255) / 256;
+        const int groups = M / spk::kColRows;
+        const dim3 grid((groups + 7) / 8 * 8);
+        const auto fn = nv <= 2   ? spk::k_quant_cols<2>
+                        : nv <= 4 ? spk::k_quant_cols<4>
+                        : nv <= 6 ? spk::k_quant_cols<6>
+                        : nv <= 8 ? spk::k_quant_cols<8>
+                                  : spk::k_quant_cols<16>;
+        hipLaunchKernelGGL(fn, grid, dim3(64 * spk::kColRows), (size_t)spk::kColRows * K, st, W, M, K, Q, scale);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? SPIKE_OK : hip_fail(e, "quantizer launch");
+    }
+    // rows of 2048 values or more: a workgroup per row (at 1536 values both
+    // forms take the same time)
+    if (K % 4 == 0 && aligned(W, 16) && K >= 2048)
+        hipLaunchKernelGGL(spk::k_quant_scale_row, dim3(M), dim3(spk::kQuantBlock), 0, st, W, K, scale);
+    else if (K % 4 == 0 && aligned(W, 16))
         hipLaunchKernelGGL(spk::k_quant_scale<true>, row_grid, dim3(spk::kQuantBlock), 0, st, W, M, K, scale);
     else
         hipLaunchKernelGGL(spk::k_quant_scale<false>, row_grid, dim3(spk::kQuantBlock), 0, st, W, M, K, scale);

@@ -168,3 +168,36 @@ def test_quantizer_rejects_bad_arguments(sp):
         sp.spike_quantize_int8(W, 7, Q, s)
     with pytest.raises(ValueError):
         sp.spike_quantize_int8(W, sp.SPIKE_LAYOUT_ROW_MAJOR, Q[:8], s)
+
+
+# column-major: the one-pass kernel at every register depth (K up to 512,
+# 1024, 1536, 2048, 4096), at one row group per XCD slot and at counts that are
+# no multiple of 8, and the shapes just outside its rule (K % 4, M % 16, too
+# few rows, Q or W not 16-byte aligned); rows of 2048 values and more take the
+# workgroup-per-row scale pass there
+@pytest.mark.parametrize("M,K,w_offset,q_offset", [(1024, 4, 0, 0), (1040, 512, 0, 0), (1024, 1020, 0, 0), (1136, 1536, 0, 0),
+                                                   (1024, 2048, 0, 0), (2064, 2052, 0, 0), (2048, 4096, 0, 0),
+                                                   (1008, 516, 0, 0), (1030, 516, 0, 0), (1024, 514, 0, 0),
+                                                   (1024, 516, 4, 0), (1024, 516, 0, 4), (2048, 4100, 0, 0),
+                                                   (48, 2048, 0, 0), (5, 8200, 0, 0)])
+def test_quantizer_column_major_paths(sp, M, K, w_offset, q_offset):
+    assert_same(sp, weights(M, K, 6), sp.SPIKE_LAYOUT_COL_MAJOR, w_offset=w_offset, q_offset=q_offset)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("M", [16, 1024])
+def test_quantizer_codes_next_to_ties(sp, layout, M):
+    """Weights a few binary32 steps on either side of (n + 1/2) s for every
+    code n and for scales of all magnitudes: where the short form of the
+    division must not decide."""
+    rng = np.random.default_rng([42, 14, M])
+    W = np.empty((M, 1024), dtype=np.float32)
+    for m in range(M):
+        amax = np.float32(np.ldexp(1.0 + rng.random(), int(rng.integers(-26, 120))))
+        s = np.float32(max(amax, np.float32(1e-8)) / np.float32(127))
+        n = rng.integers(-127, 127, 1024)
+        w = ((n + 0.5) * np.float64(s)).astype(np.float32)
+        W[m] = (w.view(np.int32) + rng.integers(-3, 4, 1024).astype(np.int32)).view(np.float32)
+        W[m] = np.clip(W[m], -amax, amax)
+        W[m, 5] = amax
+    assert_same(sp, W, lay(sp, layout))
