@@ -246,6 +246,8 @@ def bench_batch1(sp, torch, timer, name, W, scale, mask_sets, copies: int, warm_
         rates = {}
         for kind, hs in (("cold", all_h), ("warm", all_h[:warm_sets])):
             st = sp.spike_stream_create(hs, 1, len(hs), nm)
+            # each token gathers its active columns, however many share a copy
+            sp.spike_stream_tune(st, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(*HEADLINE_SHAPE))
             sec_s = timer(lambda: sp.spike_stream_forward(st, dm, out), 5, 1)
             st.close()
             rates[kind] = round(counts.sum() * N / sec_s / 1e9, 1)

@@ -16,6 +16,7 @@
 #include <string>
 #include <vector>
 
+#include "colmat.hpp"
 #include "errors.hpp"
 #include "gather.hpp"
 #include "mfma.hpp"
@@ -186,6 +187,10 @@ struct spike_stream {
     bool buf = true;  // every weight matrix fits the buffer-resource kernels
     spk::StreamOperands* d_ops = nullptr;  // device operand table [n_sets][n_proj]
     spk::StreamLayout layout{};
+    spk::ColumnOrder order{};     // projections by falling K, for the matrix-core form
+    bool shape_pinned = false;    // a launch shape was set: the gather runs
+    bool mat_ok = false;          // sizes and alignment allow the matrix-core form
+    int64_t set_bytes = 0;        // weight bytes of one set
     std::vector<const void*> weights;  // to re-check alignment when the shape changes
 };
 
@@ -212,6 +217,53 @@ void launch_stream_t(const spike_stream* s, int n_tiles, unsigned units, const u
     hipLaunchKernelGGL((spk::k_stream<S, BUF>), dim3(units), dim3(S::BLOCK), dyn, st, s->d_ops, s->layout, s->n_proj,
                        s->n_sets, s->N, n_tiles, s->tiles_per_unit, n_items, s->xcd_spread, masks, s->mask_stride,
                        out, s->out_stride);
+}
+
+// When a stream runs on the matrix cores (k_stream_mat reads every weight byte
+// of a copy once per 64 tokens; the gather reads the active columns once per
+// token).  Measured on 22-block stacks at rates 0.05 - 0.20, matrix cores
+// against gather: 1536 wide, 4 copies (1 GiB) 182 us against 157 at 6 tokens per
+// copy, 182 against 193 at 8, 185 against 237 at 10; 2 copies 107 against 100 at
+// 8, 108 against 132 at 10; one copy 53 against 56 at 8.  Weights that fit the
+// caches leave the gather bound by latency, and the matrix cores win at any
+// number of tokens: 2 tokens per copy, 768 wide (84 MiB) 17 us against 24, 1040
+// wide (124 MiB) 24 against 32, 256 wide 7.9 against 8.5.
+constexpr int kStreamMatMinRows = 9;
+constexpr int64_t kStreamMatSmallBytes = 128ll << 20;
+// Weights that are read once and do not fit the 256 MB Infinity Cache are
+// marked nontemporal: 1 GiB 188 us against 202 without the mark, 260 MB 57 us
+// without against 63 with it.  (Rows that do not start on a 128-byte line share
+// lines with the next tile, which the mark would drop: 1040 wide 37 us against 28.)
+constexpr int64_t kStreamNtBytes = 512ll << 20;
+
+// Runs the stream on the matrix cores if its weights, sizes and controls
+// allow that and the rule above asks for it; false: the gather serves it.
+bool launch_stream_mat(const spike_stream* s, const uint64_t* masks, float* out, hipStream_t st)
+{
+    const int sets = std::min(s->n_sets, s->n_tokens);
+    const int rows = (s->n_tokens + sets - 1) / sets;  // of the fullest weight copy
+    const int64_t bytes = s->set_bytes * sets;
+    if (s->shape_pinned || !s->mat_ok || (rows < kStreamMatMinRows && bytes > kStreamMatSmallBytes))
+        return false;
+    int rt = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
+    const int max_K = s->layout.K[s->order.proj[0]];
+    while (rt > 1 && spk::column_lds(rt, max_K) > spk::kMfmaMaxLds)
+        rt /= 2;
+    const int row_tiles = (rows + 16 * rt - 1) / (16 * rt);
+    const int col_tiles = (s->N + spk::kColChannels - 1) / spk::kColChannels;
+    const bool lines = s->N % spk::kColChannels == 0;
+    const int64_t items = (int64_t)sets * s->n_proj;
+    const int64_t slots = lines ? (items * col_tiles + 7) / 8 * 8 : (items + 7) / 8 * 8 * col_tiles;
+    if (slots * row_tiles > 0x7fffffff)
+        return false;
+    const bool nt = row_tiles == 1 && lines && bytes > kStreamNtBytes;
+    const auto fn = rt == 4   ? (nt ? spk::k_stream_mat<4, true> : spk::k_stream_mat<4, false>)
+                    : rt == 2 ? (nt ? spk::k_stream_mat<2, true> : spk::k_stream_mat<2, false>)
+                              : (nt ? spk::k_stream_mat<1, true> : spk::k_stream_mat<1, false>);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(slots * row_tiles)), dim3(spk::kColBlock), spk::column_lds(rt, max_K), st,
+                       s->d_ops, s->layout, s->order, s->n_proj, s->n_sets, s->n_tokens, s->N, col_tiles, row_tiles,
+                       masks, (int)s->mask_stride, out, s->out_stride);
+    return true;
 }
 
 int alloc_workspace(spike_proj* h, int32_t max_B)
@@ -913,6 +965,10 @@ int spike_stream_create(const spike_proj_t* projs, int32_t n_proj, int32_t n_set
         delete s;
         return fail(SPIKE_EUNSUPPORTED, "token mask stride too large");
     }
+    for (int j = 0; j < n_proj; ++j)
+        s->order.proj[j] = (uint8_t)j;
+    std::stable_sort(s->order.proj, s->order.proj + n_proj,
+                     [&](uint8_t a, uint8_t b) { return s->layout.K[a] > s->layout.K[b]; });
     s->n_proj = n_proj;
     s->n_sets = n_sets;
     s->n_tokens = n_tokens;
@@ -922,6 +978,12 @@ int spike_stream_create(const spike_proj_t* projs, int32_t n_proj, int32_t n_set
     s->buf = buf;
     s->mask_stride = moff;
     s->out_stride = (int64_t)n_proj * N;
+    // 8-byte weight loads at 32-bit offsets, spike words at 32-bit offsets
+    s->mat_ok = buf && N % 8 == 0 && n_tokens * moff * (int64_t)sizeof(uint64_t) <= spk::kBufMaxBytes;
+    for (const void* w : weights)
+        s->mat_ok = s->mat_ok && reinterpret_cast<uintptr_t>(w) % 8 == 0;
+    for (int j = 0; j < n_proj; ++j)
+        s->set_bytes += (int64_t)s->layout.K[j] * N;
     s->weights = std::move(weights);
     const size_t ops_bytes = ops.size() * sizeof(spk::StreamOperands);
     hipError_t e = hipGetDevice(&s->device);
@@ -954,6 +1016,7 @@ int spike_stream_tune(spike_stream_t s, int32_t key, int32_t value)
         if (((int64_t)s->n_tokens * s->n_proj + 8) * n_tiles > 0x7fffffff)
             return fail(SPIKE_EUNSUPPORTED, "shape makes the launch too large");
         s->shape = e;
+        s->shape_pinned = value != 0;
         return SPIKE_OK;
     }
     case SPIKE_TUNE_TILES_PER_UNIT:
@@ -981,6 +1044,10 @@ int spike_stream_forward(spike_stream_t s, const uint64_t* masks, float* out, vo
         return fail(SPIKE_EINVAL, "null mask or output pointer");
     if (int rc = check_device(s->device))
         return rc;
+    if (launch_stream_mat(s, masks, out, static_cast<hipStream_t>(stream))) {
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? SPIKE_OK : hip_fail(e, "matrix-core stream launch");
+    }
     const int tile = shape_tile(s->shape);
     const int n_tiles = (s->N + tile - 1) / tile;
     const int tpu = std::min(s->tiles_per_unit, n_tiles);

@@ -574,6 +574,51 @@ def test_stream_every_shape_and_xcd_spread(sp, stack):
                 assert torch.equal(out.view(torch.int32), ref.view(torch.int32)), (hex(code), tpu, spread)
 
 
+# The stream's matrix-core form: tokens per weight copy around the 16-, 32-
+# and 64-row tiles (and uneven over the copies, and fewer tokens than
+# copies); K around the 64-column steps and 128-column double steps of its 4
+# waves; N around the 128-channel tiles; outputs and scales off the 16-byte
+# alignment.  Every output against the oracle, and the gather's bits.
+@pytest.mark.parametrize("T,n_sets,N,Ks,offset", [
+    (16, 1, 16, (1, 64, 65), 0), (33, 2, 128, (127, 128, 129), 0), (64, 2, 136, (512, 511, 100, 513), 0),
+    (65, 1, 272, (640, 33), 0), (131, 1, 264, (700,), 0), (9, 16, 256, (192, 1030), 0), (250, 4, 144, (384, 1537), 4),
+    (70, 3, 1536, (1536, 6144), 0), (20, 1, 24, (16384,), 0)])
+def test_stream_matrix_core_form(sp, T, n_sets, N, Ks, offset):
+    rng = np.random.default_rng([42, 31, T, N])
+    host, hs = [], []
+    for s in range(n_sets):
+        for K in Ks:
+            W = rng.integers(-128, 128, (K, N)).astype(np.int8)
+            sc = rng.uniform(-1e-2, 1e-2, N).astype(np.float32)
+            scd = dev(np.concatenate([np.zeros(offset // 4, np.float32), sc]))[offset // 4:]
+            host.append((W, sc))
+            hs.append(sp.spike_proj_create_reserved(dev(W), scd, 1, gather_only=True))
+    # junk bits past each K
+    masks = [rng.integers(0, 2 ** 64, (T, wl.words_per_row(K)), dtype=np.uint64) &
+             rng.integers(0, 2 ** 64, (T, wl.words_per_row(K)), dtype=np.uint64) for K in Ks]
+    st = sp.spike_stream_create(hs, len(Ks), n_sets, T)
+    outs = []
+    for pinned in (False, True):
+        if pinned:  # the gather
+            sp.spike_stream_tune(st, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(1, 64, 4, 256))
+        flat = torch.full((offset // 4 + T * len(Ks) * N + 8,), 3.5, device="cuda")
+        out = flat[offset // 4:offset // 4 + T * len(Ks) * N].view(T, len(Ks) * N)
+        sp.spike_stream_forward(st, dmask(np.concatenate(masks, axis=1)), out)
+        torch.cuda.synchronize()
+        assert (flat[:offset // 4] == 3.5).all() and (flat[-8:] == 3.5).all()
+        outs.append(out.cpu().numpy())
+    np.testing.assert_array_equal(bits32(outs[0]), bits32(outs[1]))
+    for j, K in enumerate(Ks):
+        for s in range(min(n_sets, T)):
+            W, sc = host[s * len(Ks) + j]
+            m = masks[j][s::n_sets].copy()
+            if K % 64:
+                m[:, -1] &= np.uint64((1 << (K % 64)) - 1)
+            ref = oracle.spike_forward(W, sc, np.ascontiguousarray(m), threads=8)
+            np.testing.assert_array_equal(bits32(outs[0][s::n_sets, j * N:(j + 1) * N]), bits32(ref))
+    st.close()
+
+
 @pytest.mark.parametrize("B", [1, 17, 64, 65, 130])
 @pytest.mark.parametrize("K,N", [(100, 64), (1536, 1536), (4097, 192), (6144, 1024)])
 def test_matrix_core_path(sp, B, K, N):
