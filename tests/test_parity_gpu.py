@@ -619,6 +619,47 @@ def test_stream_matrix_core_form(sp, T, n_sets, N, Ks, offset):
     st.close()
 
 
+# The fused launch over the active columns (up to 8 rows, enough weight
+# bytes): K around its 16-column, 64-entry and 8192-column pieces, N at a ragged
+# last tile, rows from silent to full, weights off the 8-byte alignment (which
+# keep the packed form), and sizes just below and above its byte rule.
+@pytest.mark.parametrize("B,N,repeat,w_offset", [(1, 272, 9, 0), (2, 272, 9, 0), (5, 272, 9, 0), (8, 400, 9, 0), (7, 416, 9, 4),
+                                                 (1, 272, 2, 0), (9, 400, 9, 0)])
+def test_fused_active_columns(sp, B, N, repeat, w_offset):
+    rng = np.random.default_rng([42, 32, B, N])
+    Ks = (16384, 8200, 6177, 1536, 100, 33, 1)
+    weights = []
+    for K in Ks:
+        W = rng.integers(-128, 128, (K, N)).astype(np.int8)
+        sc = rng.uniform(-1e-2, 1e-2, N).astype(np.float32)
+        Wd = dev(np.concatenate([np.zeros(w_offset, np.int8), W.ravel()]))[w_offset:].view(K, N)
+        weights.append((W, sc, sp.spike_proj_create_reserved(Wd, dev(sc), B)))
+    items = weights * repeat
+    assert len(items) <= 64
+    masks = []
+    for i, (W, _, _) in enumerate(items):
+        K = W.shape[0]
+        bits = rng.random((B, K)) < (0.1, 0.02, 0.5, 1.0, 0.0)[i % 5]
+        if B > 1:
+            bits[i % B] = i % 3 == 0  # a silent or full row among the others
+        m = wl.pack_bits(bits)
+        if K % 64:
+            m[:, -1] |= np.uint64((~((1 << (K % 64)) - 1)) & 0xFFFFFFFFFFFFFFFF)  # junk past K
+        masks.append(m)
+    flat = torch.full((len(items) * B * N + 8,), 3.5, device="cuda")
+    sp.spike_stack_forward_fused([h for _, _, h in items], dmask(np.concatenate([m.ravel() for m in masks])), B,
+                                 flat[:len(items) * B * N])
+    torch.cuda.synchronize()
+    assert (flat[len(items) * B * N:] == 3.5).all()
+    got = flat[:len(items) * B * N].cpu().numpy().reshape(len(items), B, N)
+    for i, ((W, sc, _), m) in enumerate(zip(items, masks)):
+        K = W.shape[0]
+        m = m.copy()
+        if K % 64:
+            m[:, -1] &= np.uint64((1 << (K % 64)) - 1)
+        np.testing.assert_array_equal(bits32(got[i]), bits32(oracle.spike_forward(W, sc, m, threads=8)), err_msg=f"item {i}")
+
+
 @pytest.mark.parametrize("B", [1, 17, 64, 65, 130])
 @pytest.mark.parametrize("K,N", [(100, 64), (1536, 1536), (4097, 192), (6144, 1024)])
 def test_matrix_core_path(sp, B, K, N):
