@@ -184,7 +184,7 @@ def bench_decode_stack(sp, torch, wl, timer, args):
     if not args.no_latency:
         static_mask = torch.zeros(masks.shape[1], dtype=torch.int64, device="cuda")
         static_out = torch.zeros(len(order) * N, device="cuda")
-        g = graph_of(torch, lambda: sp.spike_stack_forward(handles, static_mask, 1, static_out))
+        g = graph_of(torch, lambda: stack_in_order(sp, handles, static_mask, 1, static_out))
         nt = min(args.latency_tokens, T)
         evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(nt)]
         # Keep the device behind the host: a spin kernel at the head of every
@@ -220,6 +220,17 @@ def bench_decode_stack(sp, torch, wl, timer, args):
 
 
 MALL_BYTES = 256 << 20  # MI355X Infinity Cache
+
+
+def stack_in_order(sp, handles, masks, B: int, out):
+    """One launch per projection, in order: a decoder's chain, in which each
+    projection's spikes come from the one before."""
+    m = o = 0
+    masks, out = masks.reshape(-1), out.reshape(-1)
+    for h in handles:
+        nm, no = B * ((h.K + 63) // 64), B * h.N
+        sp.spike_proj_forward(h, masks[m:m + nm], B, out[o:o + no])
+        m, o = m + nm, o + no
 
 
 def bench_batch1(sp, torch, timer, name, W, scale, mask_sets, copies: int, warm_sets: int, calls: int):
@@ -472,9 +483,10 @@ def bench_batched_stack(sp, torch, wl, timer, steps: int = 16, B: int = 64):
     dm = [torch.from_numpy(m.view(np.int64)).cuda() for m in per_step]
     out = torch.empty(sum(B * h.N for h in handles), device="cuda")
     r = {"B": B, "steps": steps, "union_bytes_per_step": union}
+    in_order = lambda *a: stack_in_order(sp, *a)  # noqa: E731
     for name, path, fn in (("fused", sp.SPIKE_PATH_AUTO, sp.spike_stack_forward_fused),
-                           ("mfma", sp.SPIKE_PATH_AUTO, sp.spike_stack_forward),
-                           ("gather", sp.SPIKE_PATH_GATHER, sp.spike_stack_forward)):
+                           ("mfma", sp.SPIKE_PATH_AUTO, in_order),
+                           ("gather", sp.SPIKE_PATH_GATHER, in_order)):
         for h in handles:
             sp.spike_proj_tune(h, sp.SPIKE_TUNE_PATH, path)
         g = graph_of(torch, lambda: [fn(handles, dm[s], B, out) for s in range(steps)])

@@ -236,7 +236,11 @@ int spike_compact(const uint64_t *spike_bitmask, int32_t B, int32_t K, int32_t *
  * order on `stream`, each on B rows.  Spike masks and outputs are packed per
  * projection, in order: projection j reads B rows of ceil(K_j/64) words
  * starting at word offset sum_{i<j} B*ceil(K_i/64) of `masks`, and writes
- * B*N_j floats starting at sum_{i<j} B*N_i of `out`. */
+ * B*N_j floats starting at sum_{i<j} B*N_i of `out`.  Where `masks` and
+ * `out` do not overlap no projection can read another's results, and up to 64
+ * rows of handles that share N, hold a matrix-core copy and have no launch
+ * control set run in one launch, as spike_stack_forward_fused does; otherwise
+ * every projection has its own launch, in order.  Results are identical. */
 int spike_stack_forward(const spike_proj_t *projs, int32_t n_proj, const uint64_t *masks, int32_t B,
                         float *out, void *stream);
 

@@ -597,6 +597,97 @@ int static_scratch(int dev, hipStream_t st, uint32_t** out)
     return SPIKE_OK;
 }
 
+// The projections of spike_stack_forward_fused in one launch (arguments
+// checked); SPIKE_EUNSUPPORTED where they cannot run together.
+int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* masks, int32_t B, float* out, void* stream)
+{
+    const int32_t N = projs[0]->N;
+    int32_t min_K = projs[0]->K;
+    int max_wpr = 0;
+    for (int j = 0; j < n_proj; ++j) {
+        if (projs[j]->N != N)
+            return fail(SPIKE_EUNSUPPORTED, "all projections of a fused launch must share N (%d vs %d)", projs[j]->N, N);
+        if (projs[j]->device != projs[0]->device)
+            return fail(SPIKE_EINVAL, "projections live on different devices");
+        min_K = std::min(min_K, projs[j]->K);
+        max_wpr = std::max(max_wpr, projs[j]->wpr);
+    }
+    if (int rc = check_device(projs[0]->device))
+        return rc;
+    // one ring plan for all items, chosen for the shortest K (every wave needs a k-step)
+    // Tiles of up to 64 rows by 48 channels, two k-steps in flight per wave;
+    // 8 waves for 64-row tiles (measured on the 64-row decode stack, 1408
+    // workgroups over 44 projections: 49 us per step against 57 us with 16
+    // waves, 53 with 4), 16 for the narrower tiles of smaller batches; the
+    // first handle's matrix-core tuning knobs override it for the whole
+    // launch.
+    const spike_proj* h0 = projs[0];
+    const int sets = N / spk::kMfmaNAlign;
+    spk::MfmaPlan p{};
+    p.rt = B <= 16 ? 1 : B <= 32 ? 2 : 4;
+    p.cs = sets % 3 == 0 ? 3 : sets % 2 == 0 ? 2 : 1;
+    p.kw = p.rt >= 4 ? 8 : 16;
+    p.d = 2;
+    if (h0->mfma_row_tile > 0)
+        p.rt = h0->mfma_row_tile;
+    if (h0->mfma_col_sets > 0)
+        p.cs = h0->mfma_col_sets;
+    if (h0->mfma_waves > 0)
+        p.kw = h0->mfma_waves;
+    if (h0->mfma_depth > 0)
+        p.d = h0->mfma_depth;
+    if (N % spk::kMfmaNAlign != 0 || !spk::mfma_ring_plan(p, (int)words_per_row(min_K), N))
+        return fail(SPIKE_EUNSUPPORTED, "no matrix-core plan serves N = %d, K >= %d, B = %d in one launch", N, min_K, B);
+    spk::MfmaItems items{};
+    int64_t moff = 0, ooff = 0;
+    for (int j = 0; j < n_proj; ++j) {
+        const spike_proj* h = projs[j];
+        if (const char* why = mfma_refusal(h->K, N, h->packed != nullptr, B, p))
+            return fail(SPIKE_EUNSUPPORTED, "projection %d (K = %d) cannot run on the matrix cores with B = %d: %s", j,
+                        h->K, B, why);
+        items.P[j] = h->packed;
+        items.scale[j] = h->scale;
+        items.mask_off[j] = moff;
+        items.out_off[j] = ooff;
+        items.wpr[j] = h->wpr;
+        moff += (int64_t)B * h->wpr;
+        ooff += (int64_t)B * N;
+    }
+    if (spk::mfma_lds_bytes(p.rt, p.cs, max_wpr) > spk::kMfmaMaxLds)
+        return fail(SPIKE_EUNSUPPORTED, "the staged spike words of the longest projection exceed the LDS budget");
+    hipError_t e = hipSuccess;
+    if (!launch_active_items(projs, n_proj, items, masks, B, out, static_cast<hipStream_t>(stream), &e))
+        e = spk::launch_mfma_items(p, items, n_proj, max_wpr, N, masks, B, out, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? SPIKE_OK : hip_fail(e, "fused matrix-core launch");
+}
+
+// Whether spike_stack_forward runs its projections in one launch.  Their
+// spikes are all given when the call is made, so their order could only show
+// where one writes into the spikes of another: the masks and the outputs must
+// not overlap.  Handles with any launch control set keep their own launches.
+// Measured for one row of the 44-projection stack on cold weights: one launch
+// 17 us, 44 launches 174 us (about 2 us of each is the launch); up to 64 rows
+// one launch is the fused call's measured range (57 us against 231 at 64).
+constexpr int kStackFusedMaxRows = 64;
+
+bool stack_in_one_launch(const spike_proj_t* projs, int32_t n_proj, const uint64_t* masks, int32_t B, const float* out)
+{
+    if (n_proj < 2 || n_proj > spk::kMfmaMaxItems || B > kStackFusedMaxRows)
+        return false;
+    int64_t words = 0, floats = 0;
+    for (int j = 0; j < n_proj; ++j) {
+        const spike_proj* h = projs[j];
+        if (!h->packed || h->N != projs[0]->N || h->device != projs[0]->device || h->path != SPIKE_PATH_AUTO ||
+            B < h->mfma_min_b || h->mfma_row_tile > 0 || h->mfma_col_sets > 0 || h->mfma_waves > 0 || h->mfma_depth > 0)
+            return false;
+        words += (int64_t)B * h->wpr;
+        floats += (int64_t)B * h->N;
+    }
+    const uintptr_t m0 = reinterpret_cast<uintptr_t>(masks), m1 = m0 + words * sizeof(uint64_t);
+    const uintptr_t o0 = reinterpret_cast<uintptr_t>(out), o1 = o0 + floats * sizeof(float);
+    return m1 <= o0 || o1 <= m0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -862,6 +953,12 @@ int spike_stack_forward(const spike_proj_t* projs, int32_t n_proj, const uint64_
         return SPIKE_OK;
     if (!masks || !out)
         return fail(SPIKE_EINVAL, "null mask or output pointer");
+    if (stack_in_one_launch(projs, n_proj, masks, B, out)) {
+        const int rc = forward_fused(projs, n_proj, masks, B, out, stream);
+        if (rc != SPIKE_EUNSUPPORTED)
+            return rc;
+        spk::last_error.clear();  // no plan serves them together
+    }
     int64_t moff = 0, ooff = 0;
     for (int j = 0; j < n_proj; ++j) {
         if (int rc = spike_proj_forward(projs[j], masks + moff, B, out + ooff, stream))
@@ -892,64 +989,7 @@ int spike_stack_forward_fused(const spike_proj_t* projs, int32_t n_proj, const u
         return SPIKE_OK;
     if (!masks || !out)
         return fail(SPIKE_EINVAL, "null mask or output pointer");
-    const int32_t N = projs[0]->N;
-    int32_t min_K = projs[0]->K;
-    int max_wpr = 0;
-    for (int j = 0; j < n_proj; ++j) {
-        if (projs[j]->N != N)
-            return fail(SPIKE_EUNSUPPORTED, "all projections of a fused launch must share N (%d vs %d)", projs[j]->N, N);
-        if (projs[j]->device != projs[0]->device)
-            return fail(SPIKE_EINVAL, "projections live on different devices");
-        min_K = std::min(min_K, projs[j]->K);
-        max_wpr = std::max(max_wpr, projs[j]->wpr);
-    }
-    if (int rc = check_device(projs[0]->device))
-        return rc;
-    // one ring plan for all items, chosen for the shortest K (every wave needs a k-step)
-    // Tiles of up to 64 rows by 48 channels, two k-steps in flight per wave;
-    // 8 waves for 64-row tiles (measured on the 64-row decode stack, 1408
-    // workgroups over 44 projections: 49 us per step against 57 us with 16
-    // waves, 53 with 4), 16 for the narrower tiles of smaller batches; the
-    // first handle's matrix-core tuning knobs override it for the whole
-    // launch.
-    const spike_proj* h0 = projs[0];
-    const int sets = N / spk::kMfmaNAlign;
-    spk::MfmaPlan p{};
-    p.rt = B <= 16 ? 1 : B <= 32 ? 2 : 4;
-    p.cs = sets % 3 == 0 ? 3 : sets % 2 == 0 ? 2 : 1;
-    p.kw = p.rt >= 4 ? 8 : 16;
-    p.d = 2;
-    if (h0->mfma_row_tile > 0)
-        p.rt = h0->mfma_row_tile;
-    if (h0->mfma_col_sets > 0)
-        p.cs = h0->mfma_col_sets;
-    if (h0->mfma_waves > 0)
-        p.kw = h0->mfma_waves;
-    if (h0->mfma_depth > 0)
-        p.d = h0->mfma_depth;
-    if (N % spk::kMfmaNAlign != 0 || !spk::mfma_ring_plan(p, (int)words_per_row(min_K), N))
-        return fail(SPIKE_EUNSUPPORTED, "no matrix-core plan serves N = %d, K >= %d, B = %d in one launch", N, min_K, B);
-    spk::MfmaItems items{};
-    int64_t moff = 0, ooff = 0;
-    for (int j = 0; j < n_proj; ++j) {
-        const spike_proj* h = projs[j];
-        if (const char* why = mfma_refusal(h->K, N, h->packed != nullptr, B, p))
-            return fail(SPIKE_EUNSUPPORTED, "projection %d (K = %d) cannot run on the matrix cores with B = %d: %s", j,
-                        h->K, B, why);
-        items.P[j] = h->packed;
-        items.scale[j] = h->scale;
-        items.mask_off[j] = moff;
-        items.out_off[j] = ooff;
-        items.wpr[j] = h->wpr;
-        moff += (int64_t)B * h->wpr;
-        ooff += (int64_t)B * N;
-    }
-    if (spk::mfma_lds_bytes(p.rt, p.cs, max_wpr) > spk::kMfmaMaxLds)
-        return fail(SPIKE_EUNSUPPORTED, "the staged spike words of the longest projection exceed the LDS budget");
-    hipError_t e = hipSuccess;
-    if (!launch_active_items(projs, n_proj, items, masks, B, out, static_cast<hipStream_t>(stream), &e))
-        e = spk::launch_mfma_items(p, items, n_proj, max_wpr, N, masks, B, out, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? SPIKE_OK : hip_fail(e, "fused matrix-core launch");
+    return forward_fused(projs, n_proj, masks, B, out, stream);
 }
 
 int spike_stream_create(const spike_proj_t* projs, int32_t n_proj, int32_t n_sets, int32_t n_tokens,

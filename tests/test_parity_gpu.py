@@ -318,6 +318,50 @@ def test_fused_stack_refusals(sp):
     assert ei.value.code == sp.SPIKE_EUNSUPPORTED
 
 
+@pytest.mark.parametrize("B", [1, 9, 64, 65])
+@pytest.mark.parametrize("variant", ["one launch", "other N", "gather handle", "gather path", "overlap"])
+def test_stack_forward_routes(sp, B, variant):
+    """spike_stack_forward against the oracle where it may use one launch and
+    where it may not: channel counts that differ, a handle without the packed
+    copy, a pinned path, and spikes that an earlier projection's outputs
+    overwrite (read after they are written, as in separate launches)."""
+    rng = np.random.default_rng([42, 33, B])
+    Ks, Ns = (200, 64, 1000), (48, 48, 48 if variant != "other N" else 64)
+    host = [(rng.integers(-127, 128, (K, N)).astype(np.int8), rng.uniform(1e-3, 1e-2, N).astype(np.float32))
+            for K, N in zip(Ks, Ns)]
+    hs = [sp.spike_proj_create_reserved(dev(W), dev(s), B, gather_only=variant == "gather handle" and i == 1)
+          for i, (W, s) in enumerate(host)]
+    if variant == "gather path":
+        sp.spike_proj_tune(hs[2], sp.SPIKE_TUNE_PATH, sp.SPIKE_PATH_GATHER)
+    masks = [wl.pack_bits(rng.random((B, K)) < 0.2) for K in Ks]
+    n_mask, n_out = sum(m.size for m in masks), sum(B * N for N in Ns)
+    if variant == "overlap":  # the first projection writes over the spikes of the last two
+        buf = torch.zeros(n_mask + n_out, dtype=torch.int64, device="cuda")
+        first = masks[0].size
+        d_masks, out = buf[:n_mask], buf[first:].view(torch.float32)[:n_out]
+        d_masks.copy_(dmask(np.concatenate([m.ravel() for m in masks])))
+        torch.cuda.synchronize()
+        sp.spike_stack_forward(hs, d_masks, B, out)
+        torch.cuda.synchronize()
+        ref_buf = np.zeros(n_mask + n_out, np.uint64)
+        ref_buf[:n_mask] = np.concatenate([m.ravel() for m in masks])
+        ref_out, mo, oo = ref_buf[first:].view(np.float32), 0, 0
+        for (W, s), m in zip(host, masks):
+            words = ref_buf[mo:mo + m.size].reshape(m.shape).copy()
+            if W.shape[0] % 64:
+                words[:, -1] &= np.uint64((1 << (W.shape[0] % 64)) - 1)
+            y = oracle.spike_forward(W, s, words)
+            ref_out[oo:oo + y.size] = y.ravel()
+            mo, oo = mo + m.size, oo + y.size
+        np.testing.assert_array_equal(bits32(out.cpu().numpy()), bits32(ref_out[:n_out]))
+        return
+    out = torch.full((n_out,), float("nan"), device="cuda")
+    sp.spike_stack_forward(hs, dmask(np.concatenate([m.ravel() for m in masks])), B, out)
+    torch.cuda.synchronize()
+    ref = np.concatenate([oracle.spike_forward(W, s, m).ravel() for (W, s), m in zip(host, masks)])
+    np.testing.assert_array_equal(bits32(out.cpu().numpy()), bits32(ref))
+
+
 def test_batch_zero_is_a_noop(sp):
     p = wl.small_problem(100, 64, 1, 0.5)
     h, *_ = make(sp, p["W"], p["scale"])
