@@ -97,8 +97,8 @@ def _check(rc: int, where: str) -> None:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current stream, without building a Stream object (0.2 us against 2.9)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -226,22 +226,29 @@ def _handle_array(handles):
     return arr
 
 
+def _stack_sizes(handles):
+    """Mask words and output floats of one row of the projections."""
+    words = floats = 0
+    for h in handles:
+        words += (h.K + 63) >> 6
+        floats += h.N
+    return words, floats
+
+
 def spike_stack_forward(handles, masks: torch.Tensor, B: int, out: torch.Tensor, stream=None) -> None:
     """Run the projections in order; masks/out packed per projection (see the header)."""
     arr = _handle_array(handles)
-    mwords = sum(B * words_per_row(h.K) for h in handles)
-    ofl = sum(B * h.N for h in handles)
-    _check(_lib.spike_stack_forward(arr, len(handles), _dev_ptr(masks, "masks", mwords * 8), int(B),
-                                    _dev_ptr(out, "out", ofl * 4), _stream(stream)), "spike_stack_forward")
+    words, floats = _stack_sizes(handles)
+    _check(_lib.spike_stack_forward(arr, len(handles), _dev_ptr(masks, "masks", B * words * 8), int(B),
+                                    _dev_ptr(out, "out", B * floats * 4), _stream(stream)), "spike_stack_forward")
 
 
 def spike_stack_forward_fused(handles, masks: torch.Tensor, B: int, out: torch.Tensor, stream=None) -> None:
     """All projections in one matrix-core launch (inputs all given); same layout as spike_stack_forward."""
     arr = _handle_array(handles)
-    mwords = sum(B * words_per_row(h.K) for h in handles)
-    ofl = sum(B * h.N for h in handles)
-    _check(_lib.spike_stack_forward_fused(arr, len(handles), _dev_ptr(masks, "masks", mwords * 8), int(B),
-                                          _dev_ptr(out, "out", ofl * 4), _stream(stream)), "spike_stack_forward_fused")
+    words, floats = _stack_sizes(handles)
+    _check(_lib.spike_stack_forward_fused(arr, len(handles), _dev_ptr(masks, "masks", B * words * 8), int(B),
+                                          _dev_ptr(out, "out", B * floats * 4), _stream(stream)), "spike_stack_forward_fused")
 
 
 class SpikeStream:
