@@ -51,6 +51,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "gather.hpp"  // u32x4
 
 namespace spk {
@@ -483,6 +485,226 @@ __global__ __launch_bounds__(64 * KW) void k_mfma_items(const MfmaItems items, i
                                            nullptr);
 }
 
+// ---------------------------------------------------------------------------
+// Wide form, for batches that fill the chip with 128-row x 128-channel tiles.
+//
+// The tiles above are short-lived: 64 rows of a 6144-input call are 6 dependent
+// k-steps per wave between fixed latencies, and every 64 rows read all weights
+// again from L2.  Here a workgroup of 8 waves owns 128 rows x 128 channels: wave
+// (kw, cw) runs every fourth k-step for 64 of the channels and all rows, 16
+// v_mfma_i32_32x32x32_i8 per step for 4 KB of weights, loaded straight to its
+// registers kWideDepth steps ahead.  No barrier falls between the staging of the
+// spike words and the sum over the four k-waves (the first writes, the others
+// add, in LDS).  The tiles of one channel range follow each other on one XCD.
+//
+// It is bound by the matrix pipe and the vector instructions that expand the
+// spike bits, which share the issue slots: 6144 -> 1536 at 2500 rows 29.2 us
+// (1.6 POPS) against 43.1 in 64 x 48 tiles, 27.0 with the bits not expanded in a
+// timing copy; 1536 -> 1536 13.5 against 24.8, 4096 -> 4096 at 1300 rows 38.9
+// against 62.4, 512 -> 4096 at 2500 rows 24.8 against 36.9.  With 16x16x64
+// instructions the first takes 30.5; 3 or 4 steps ahead change nothing, and a
+// loop with a condition around each step (its waits then let no load stay in
+// flight) took 32.5.
+// ---------------------------------------------------------------------------
+typedef int32_t mf_i32x16 __attribute__((ext_vector_type(16)));
+constexpr int kWideKW = 4, kWideCW = 2;  // waves along K and along the channels
+constexpr int kWideRows = 128, kWideChannels = 128;
+constexpr int kWideBlock = 64 * kWideKW * kWideCW;
+constexpr int kWideDepth = 2;
+constexpr int kWidePitch = kWideChannels + 4;  // INT32 sums of a row, 16-byte aligned rows in other banks
+constexpr int kWideMaxLds = 136 * 1024;
+inline int wide_lds_bytes(int wpr)
+{
+    return std::max(kWideRows * mfma_stage_pitch(wpr) * (int)sizeof(uint64_t), kWideRows * kWidePitch * (int)sizeof(int32_t));
+}
+
+template <bool ACC>
+__global__ __launch_bounds__(kWideBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_mfma_wide(
+    const int8_t* __restrict__ P, const float* __restrict__ scale, int N, const uint64_t* __restrict__ mask, int wpr,
+    int B, int n_rowtiles, int n_tiles, float* __restrict__ out, int32_t* __restrict__ acc_out)
+{
+    constexpr int MT = kWideRows / 32, CT = kWideChannels / 32 / kWideCW, D = kWideDepth;
+    extern __shared__ __align__(16) uint8_t lds[];
+    // workgroup b runs on XCD b % 8, which takes one eighth of the tiles, rows fastest
+    const int per = (n_tiles + 7) / 8;
+    const int tile = (int)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    if ((int)(blockIdx.x / 8) >= per || tile >= n_tiles)  // the whole workgroup
+        return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int kw = wave % kWideKW, cw = wave / kWideKW;
+    const int l = threadIdx.x % 64, g = l / 32, c32 = l % 32;
+    const int m0 = tile % n_rowtiles * kWideRows;
+    const int t0 = tile / n_rowtiles * (kWideChannels / 16);  // first channel set of the tile
+    const int n_steps = (wpr - kw + kWideKW - 1) / kWideKW;
+
+    // Operands of v_mfma_i32_32x32x32_i8: lane l holds row or channel l % 32 and
+    // 16 columns of a 32-column half step.  A pair of channel sets gives the 32
+    // channels, lanes 16 .. 31 of each 32 reading the second set.  A step past the
+    // wave's last and a channel set past N are read at the end of the resource:
+    // zeros, without a memory request.
+    const int w_records = (N / 16) * wpr * kMfmaSetStepBytes;
+    const __amdgpu_buffer_rsrc_t prsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(P), 0, w_records, kBufferWordFormat);
+    uint32_t lane_off[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const int set = t0 + 2 * CT * cw + 2 * t + c32 / 16;
+        lane_off[t] = 16 * set < N ? (uint32_t)(set * wpr * kMfmaSetStepBytes + (16 * g + c32 % 16) * 16) : kOutOfRange;
+    }
+    auto load_w = [&](int i, u32x4 (&wv)[2 * CT]) {
+        const int s = kw + i * kWideKW;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                wv[CT * h + t] = __builtin_amdgcn_raw_buffer_load_b128(
+                    prsrc, lane_off[t], i < n_steps ? s * kMfmaSetStepBytes + 512 * h : w_records, 0);
+    };
+    u32x4 wbuf[D][2 * CT];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        load_w(d, wbuf[d]);
+
+    // the tile's spike words; rows at or past B read as 0
+    const int pitch = wpr | 1;
+    uint64_t* xs = reinterpret_cast<uint64_t*>(lds);
+    {
+        const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint64_t*>(mask), 0, B * wpr * (int)sizeof(uint64_t), kBufferWordFormat);
+        const int total = kWideRows * wpr;
+        constexpr int kBatch = 8;
+        for (int base = threadIdx.x; base < total; base += kBatch * kWideBlock) {
+            u32x2 v[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                v[u] = __builtin_amdgcn_raw_buffer_load_b64(
+                    mrsrc, (m0 * wpr + min(base + u * kWideBlock, total - 1)) * (int)sizeof(uint64_t), 0, 0);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int e = base + u * kWideBlock;
+                const int r = e / wpr;
+                if (e < total)
+                    xs[e + r * (pitch - wpr)] = __builtin_bit_cast(uint64_t, v[u]);
+            }
+        }
+    }
+    __syncthreads();
+
+    mf_i32x16 acc[MT][CT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                acc[mt][t][j] = 0;
+    const uint16_t* xs16 = reinterpret_cast<const uint16_t*>(xs);
+    auto read_bits = [&](int i, uint32_t (&b)[2 * MT]) {
+        const int s = kw + max(min(i, n_steps - 1), 0) * kWideKW;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                b[MT * h + mt] = xs16[((32 * mt + c32) * pitch + s) * 4 + 2 * h + g];
+    };
+    auto products = [&](const uint32_t (&b)[2 * MT], const u32x4 (&wv)[2 * CT]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const uint32_t x = b[MT * h + mt];
+                const mf_i32x4 a = {(int32_t)expand_nibble(x), (int32_t)expand_nibble(x >> 4), (int32_t)expand_nibble(x >> 8),
+                                    (int32_t)expand_nibble(x >> 12)};
+#pragma unroll
+                for (int t = 0; t < CT; ++t)
+                    acc[mt][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, __builtin_bit_cast(mf_i32x4, wv[CT * h + t]),
+                                                                       acc[mt][t], 0, 0, 0);
+            }
+    };
+    // The loop runs whole rounds of D steps without conditions, so that every
+    // wait knows how many younger loads are in flight; the spike bits of the
+    // next step are read one step ahead.
+    uint32_t bits[2 * MT];
+    read_bits(0, bits);
+    auto step = [&](int i, u32x4 (&wv)[2 * CT]) {
+        uint32_t nb[2 * MT];
+        read_bits(i + 1, nb);
+        products(bits, wv);
+        load_w(i + D, wv);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < 2 * MT; ++m)
+            bits[m] = nb[m];
+    };
+    const int n_full = n_steps / D * D;
+    int i0 = 0;
+    for (; i0 < n_full; i0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            step(i0 + d, wbuf[d]);
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (i0 + d < n_steps)
+            step(i0 + d, wbuf[d]);
+
+    // register j of acc[mt][t]: row 32 mt + 8 (j / 4) + 4 g + j % 4, channel 32 t + l % 32 of the wave's 64
+    int32_t* sums = reinterpret_cast<int32_t*>(lds);
+    int32_t* mine = sums + 4 * g * kWidePitch + 32 * CT * cw + c32;
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    f(&mine[(32 * mt + 8 * (j / 4) + j % 4) * kWidePitch + 32 * t], acc[mt][t][j]);
+    };
+    __syncthreads();  // the spike words have been read
+    if (kw == 0)
+        each([](int32_t* at, int32_t v) { *at = v; });
+    __syncthreads();
+    if (kw != 0)
+        each([](int32_t* at, int32_t v) { atomicAdd(at, v); });
+    __syncthreads();
+    const int n = 16 * t0 + 4 * ((int)threadIdx.x % 32);
+    if (n >= N)
+        return;
+    const bool vec = ((reinterpret_cast<uintptr_t>(ACC ? (const void*)acc_out : (const void*)out) |
+                       (ACC ? 0 : reinterpret_cast<uintptr_t>(scale))) & 15) == 0;  // N % 16 == 0
+    f32x4 s4{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (!ACC) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            s4[e] = scale[n + e];
+    }
+    for (int r = threadIdx.x / 32; r < kWideRows && m0 + r < B; r += kWideBlock / 32) {
+        const i32x4 sum = *reinterpret_cast<const i32x4*>(sums + r * kWidePitch + n - 16 * t0);
+        const int64_t at = (int64_t)(m0 + r) * N + n;
+        if constexpr (ACC) {
+            if (vec) {
+                *reinterpret_cast<i32x4*>(acc_out + at) = sum;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc_out[at + e] = sum[e];
+            }
+        } else {
+            f32x4 y;  // exact for |sum| < 2^24, RNE beyond; one binary32 multiply each
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                y[e] = (float)sum[e] * s4[e];
+            if (vec) {
+                __builtin_nontemporal_store(y, reinterpret_cast<f32x4*>(out + at));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    out[at + e] = y[e];
+            }
+        }
+    }
+}
+
 // Launch configuration of the matrix-core path.
 struct MfmaPlan {
     int rt, cs, kw, d;
@@ -765,6 +987,36 @@ inline hipError_t launch_mfma(const MfmaPlan& p, const int8_t* P, const float* s
 #undef SPK_LAUNCH
 #undef SPK_LAUNCH_DIRECT
     return hipErrorInvalidValue;
+}
+
+// Whether B rows run in the wide form: one tile takes a compute unit about as
+// long as the other form takes for 110 - 150 of its tiles over the whole chip, so
+// each round of 256 tiles has to be full enough.  Measured, wide against 64-row
+// tiles: 6144 -> 1536, 96 tiles 26.0 us against 19.5, 144 tiles 26.6 against 28.0,
+// 240 tiles 29.2 against 43.1; 1536 -> 1536, 96 tiles 11.4 against 11.8; 4096 ->
+// 4096, 128 tiles 20.1 against 25.6; 512 -> 4096, 192 tiles 9.4 against 12.8; 2048
+// -> 256, 40 tiles 12.3 against 10.4.
+constexpr int kWideMinTiles = 144;
+inline bool mfma_wide_applies(int K, int N, int B)
+{
+    const int wpr = (K + 63) / 64;
+    const int64_t row_tiles = (B + kWideRows - 1) / kWideRows;
+    const int64_t tiles = row_tiles * ((N + kWideChannels - 1) / kWideChannels);
+    if (wide_lds_bytes(wpr) > kWideMaxLds || row_tiles * kWideRows * wpr * (int64_t)sizeof(uint64_t) >= (1ll << 31) ||
+        tiles > 0x7ffffff)
+        return false;
+    return tiles >= kWideMinTiles * ((tiles + 255) / 256);
+}
+
+inline hipError_t launch_mfma_wide(const int8_t* P, const float* scale, int K, int N, const uint64_t* mask, int B,
+                                   float* out, int32_t* acc, bool want_acc, hipStream_t st)
+{
+    const int wpr = (K + 63) / 64;
+    const int row_tiles = (B + kWideRows - 1) / kWideRows;
+    const int tiles = row_tiles * ((N + kWideChannels - 1) / kWideChannels);
+    hipLaunchKernelGGL(want_acc ? k_mfma_wide<true> : k_mfma_wide<false>, dim3((unsigned)((tiles + 7) / 8 * 8)),
+                       dim3(kWideBlock), wide_lds_bytes(wpr), st, P, scale, N, mask, wpr, B, row_tiles, tiles, out, acc);
+    return hipGetLastError();
 }
 
 }  // namespace spk

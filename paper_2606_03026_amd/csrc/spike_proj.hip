@@ -522,7 +522,12 @@ int forward_impl(spike_proj* h, const uint64_t* mask, int32_t B, float* out, int
         if (const char* why = mfma_refusal(h->K, h->N, h->packed != nullptr, B, p))
             return fail(SPIKE_EUNSUPPORTED, "matrix-core path for B = %d, K = %d, N = %d (row tile %d, channel sets "
                         "%d, waves %d, depth %d): %s", B, h->K, h->N, p.rt, p.cs, p.kw, p.d, why);
-        const hipError_t e = spk::launch_mfma(p, h->packed, h->scale, h->K, h->N, mask, B, out, acc, ACC, st);
+        // a tuned plan keeps the tiled form
+        const bool tuned = h->mfma_row_tile > 0 || h->mfma_col_sets > 0 || h->mfma_waves > 0 || h->mfma_depth > 0;
+        const hipError_t e =
+            !tuned && spk::mfma_wide_applies(h->K, h->N, B)
+                ? spk::launch_mfma_wide(h->packed, h->scale, h->K, h->N, mask, B, out, acc, ACC, st)
+                : spk::launch_mfma(p, h->packed, h->scale, h->K, h->N, mask, B, out, acc, ACC, st);
         return e == hipSuccess ? SPIKE_OK : hip_fail(e, "matrix-core launch");
     }
     return launch_gather<ACC>(h, mask, B, out, acc, st);

@@ -809,6 +809,30 @@ def test_matrix_core_extremes(sp):
     assert_parity(sp, h, W, scale, masks[:9])
 
 
+# The wide form (at least 144 tiles of 128 x 128): fewer k-steps than its 4
+# waves, step counts around whole rounds of 8, ragged last row and channel
+# tiles, the longest staged rows, and outputs off the 16-byte alignment.
+@pytest.mark.parametrize("K,N,B,p,offset", [(1, 2064, 1152, 0.5, 0), (130, 2048, 1025, 0.3, 1), (300, 2048, 1100, 0.3, 0),
+                                            (513, 1040, 2050, 0.2, 0), (1500, 1936, 1100, 0.1, 3), (8640, 1040, 2176, 0.02, 0)])
+def test_matrix_core_wide_form(sp, K, N, B, p, offset):
+    prob = wl.small_problem(K, N, B, p, seed=K + N)
+    masks = prob["masks"].copy()
+    if K % 64:
+        masks[:, -1] |= np.uint64((~((1 << (K % 64)) - 1)) & 0xFFFFFFFFFFFFFFFF)  # junk past K
+    h = sp.spike_proj_create_reserved(dev(prob["W"]), dev(prob["scale"]), B)
+    flat = torch.full((offset + B * N + 8,), 3.5, device="cuda")
+    acc = torch.full((offset + B * N + 8,), -7, dtype=torch.int32, device="cuda")
+    sp.spike_proj_forward(h, dmask(masks), B, flat[offset:offset + B * N])
+    sp.spike_proj_forward_acc(h, dmask(masks), B, acc[offset:offset + B * N])
+    torch.cuda.synchronize()
+    got, got_acc = flat.cpu().numpy(), acc.cpu().numpy()
+    assert (got[:offset] == 3.5).all() and (got[-8:] == 3.5).all() and (got_acc[:offset] == -7).all() and (got_acc[-8:] == -7).all()
+    ref = oracle.spike_forward(prob["W"], prob["scale"], prob["masks"], threads=8)
+    np.testing.assert_array_equal(bits32(got[offset:-8].reshape(B, N)), bits32(ref))
+    some = np.r_[0:5, B // 2, B - 3:B]
+    np.testing.assert_array_equal(got_acc[offset:-8].reshape(B, N)[some], oracle.spike_acc(prob["W"], prob["masks"][some]))
+
+
 def test_matrix_core_rejects_unaligned_N(sp):
     p = wl.small_problem(128, 100, 4, 0.3)
     h, *_ = make(sp, p["W"], p["scale"])
