@@ -178,6 +178,11 @@ def bench_decode_stack(sp, torch, wl, timer, args):
     sp.spike_stream_tune(cold, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(*HEADLINE_SHAPE))
     i16_gbs = step_bytes / sec16 / 1e9
     log(f"stream cold with 16-bit partial sums: {i16_gbs:.1f} GB/s ({100 * i16_gbs / HBM_PEAK_GBS:.1f}% of HBM)")
+    # the library's own choice: the tokens of a weight copy as rows of one contraction
+    sp.spike_stream_tune(cold, sp.SPIKE_TUNE_SHAPE, 0)
+    auto = timer(lambda: sp.spike_stream_forward(cold, dmasks, out), max(3, args.steps // 2), 1)
+    sp.spike_stream_tune(cold, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(*HEADLINE_SHAPE))
+    log(f"stream cold, automatic form: {auto * 1e3:.3f} ms/step")
     res = {"sec": sec, "gbs": gbs, "warm_gbs": warm_gbs, "i16_gbs": i16_gbs, "step_bytes": step_bytes,
            "host": host, "masks": masks, "Ks": Ks}
 
