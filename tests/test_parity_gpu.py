@@ -663,12 +663,40 @@ def test_stream_matrix_core_form(sp, T, n_sets, N, Ks, offset):
     st.close()
 
 
+@pytest.mark.parametrize("T", [10, 31, 40])
+def test_stream_matrix_core_form_nontemporal(sp, T):
+    """More weight bytes than the rule for nontemporal loads (one matrix named
+    by 64 projections), at each row tile: three projections against the
+    oracle, all against the gather."""
+    K, N, n = 16384, 640, 64
+    p = wl.small_problem(K, N, 1, 0.1, seed=12)
+    h = sp.spike_proj_create_reserved(dev(p["W"]), dev(p["scale"]), 1, gather_only=True)
+    rng = np.random.default_rng([42, 34, T])
+    masks = np.concatenate([wl.pack_bits(rng.random((T, K)) < 0.02) for _ in range(n)], axis=1)
+    st = sp.spike_stream_create([h] * n, n, 1, T)
+    outs = []
+    for pinned in (False, True):
+        if pinned:
+            sp.spike_stream_tune(st, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(16, 32, 4, 256, True))
+        out = torch.full((T, n * N), float("nan"), device="cuda")
+        sp.spike_stream_forward(st, dmask(masks), out)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+    got = outs[0].cpu().numpy()
+    for j in (0, 31, 63):
+        ref = oracle.spike_forward(p["W"], p["scale"], np.ascontiguousarray(masks[:, j * 256:(j + 1) * 256]), threads=8)
+        np.testing.assert_array_equal(bits32(got[:, j * N:(j + 1) * N]), bits32(ref))
+    st.close()
+
+
 # The fused launch over the active columns (up to 8 rows, enough weight
 # bytes): K around its 16-column, 64-entry and 8192-column pieces, N at a ragged
 # last tile, rows from silent to full, weights off the 8-byte alignment (which
-# keep the packed form), and sizes just below and above its byte rule.
+# keep the packed form), sizes just below and above its byte rule, and above
+# the one for nontemporal loads.
 @pytest.mark.parametrize("B,N,repeat,w_offset", [(1, 272, 9, 0), (2, 272, 9, 0), (5, 272, 9, 0), (8, 400, 9, 0), (7, 416, 9, 4),
-                                                 (1, 272, 2, 0), (9, 400, 9, 0)])
+                                                 (1, 272, 2, 0), (9, 400, 9, 0), (6, 736, 9, 0)])
 def test_fused_active_columns(sp, B, N, repeat, w_offset):
     rng = np.random.default_rng([42, 32, B, N])
     Ks = (16384, 8200, 6177, 1536, 100, 33, 1)
