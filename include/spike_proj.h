@@ -271,10 +271,11 @@ int spike_stack_forward_fused(const spike_proj_t *projs, int32_t n_proj, const u
  * (token stride sum_j ceil(K_j/64) words) and out holds n_proj * N floats.
  * create() copies a small descriptor table to the device (allocates);
  * forward() only launches.  The tokens of one weight copy are independent
- * rows: where enough of them share a copy (or the weights fit the caches),
- * N % 8 == 0 and the weights are 8-byte aligned, they run on the matrix cores
- * straight from the column-major weights; otherwise, or with SPIKE_TUNE_SHAPE
- * set, each token gathers its active columns.  Results are identical. */
+ * rows: where 9 or more share a copy (5 where the weights of all copies take up
+ * to 128 MiB), N % 8 == 0 and the weights are 8-byte aligned, they run on the
+ * matrix cores straight from the column-major weights, reading the columns that
+ * some token of a tile activates; otherwise, or with SPIKE_TUNE_SHAPE set,
+ * each token gathers its active columns.  Results are identical. */
 int spike_stream_create(const spike_proj_t *projs, int32_t n_proj, int32_t n_sets, int32_t n_tokens,
                         spike_stream_t *out_stream);
 int spike_stream_forward(spike_stream_t s, const uint64_t *masks, float *out, void *stream);

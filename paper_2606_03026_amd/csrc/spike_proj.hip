@@ -13,6 +13,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -219,16 +220,20 @@ void launch_stream_t(const spike_stream* s, int n_tiles, unsigned units, const u
                        out, s->out_stride);
 }
 
-// When a stream runs on the matrix cores (k_stream_mat reads every weight byte
-// of a copy once per 64 tokens; the gather reads the active columns once per
-// token).  Measured on 22-block stacks at rates 0.05 - 0.20, matrix cores
-// against gather: 1536 wide, 4 copies (1 GiB) 182 us against 157 at 6 tokens per
-// copy, 182 against 193 at 8, 185 against 237 at 10; 2 copies 107 against 100 at
-// 8, 108 against 132 at 10; one copy 53 against 56 at 8.  Weights that fit the
-// caches leave the gather bound by latency, and the matrix cores win at any
-// number of tokens: 2 tokens per copy, 768 wide (84 MiB) 17 us against 24, 1040
-// wide (124 MiB) 24 against 32, 256 wide 7.9 against 8.5.
-constexpr int kStreamMatMinRows = 9;
+// When a stream runs on the matrix cores: k_stream_mat reads the columns that
+// any token of a copy activates once per tile, the gather the active columns of
+// each token.  Measured on 22-block stacks at rates 0.02 / 0.05 / 0.10 / 0.20 /
+// 0.40, us, matrix cores against gather.  9 tokens per copy: 1536 wide, 4 copies
+// (990 MiB) 52 / 88 / 129 / 168 / 188 against 45 / 99 / 175 / 324 / 619; one copy 18 /
+// 31 / 49 / 63 / 70 against 14 / 28 / 49 / 89 / 168.  16: 990 MiB 73 / 121 / 164 / 189
+// / 195 against 70 / 157 / 291 / 544 / 1048.  Below 9 tokens on weights that do not
+// fit the caches the gather's shorter start counts for more.  Smaller weights
+// leave the gather bound by latency.  5 tokens per copy: 512 wide, 4 copies (110
+// MiB) 12 / 13 / 19 / 24 / 30 against 8 / 11 / 16 / 28 / 50; 768 wide, 10 blocks (28
+// MiB) 8 / 10 / 11 / 15 / 18 against 6 / 10 / 15 / 25 / 46; 256 wide, 4 blocks 6.6 / 7.4 /
+// 7.4 / 7.3 / 7.3 against 4.4 / 5.7 / 7.5 / 11 / 18.  The host cannot know the rate; the
+// lines lie where a decoder's usual rates (about 0.1) break even.
+constexpr int kStreamMatMinRows = 9, kStreamMatSmallMinRows = 5;
 constexpr int64_t kStreamMatSmallBytes = 128ll << 20;
 // Weights that are read once and do not fit the 256 MB Infinity Cache are
 // marked nontemporal: 1 GiB 188 us against 202 without the mark, 260 MB 57 us
@@ -243,11 +248,11 @@ bool launch_stream_mat(const spike_stream* s, const uint64_t* masks, float* out,
     const int sets = std::min(s->n_sets, s->n_tokens);
     const int rows = (s->n_tokens + sets - 1) / sets;  // of the fullest weight copy
     const int64_t bytes = s->set_bytes * sets;
-    if (s->shape_pinned || !s->mat_ok || (rows < kStreamMatMinRows && bytes > kStreamMatSmallBytes))
+    if (s->shape_pinned || !s->mat_ok || rows < (bytes > kStreamMatSmallBytes ? kStreamMatMinRows : kStreamMatSmallMinRows))
         return false;
     int rt = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
-    const int max_K = s->layout.K[s->order.proj[0]];
-    while (rt > 1 && spk::column_lds(rt, max_K) > spk::kMfmaMaxLds)
+    const int max_K = s->order.K[0];
+    while (rt > 1 && spk::column_words(rt, max_K) > spk::kColumnMaxWords)
         rt /= 2;
     const int row_tiles = (rows + 16 * rt - 1) / (16 * rt);
     const int col_tiles = (s->N + spk::kColChannels - 1) / spk::kColChannels;
@@ -261,7 +266,7 @@ bool launch_stream_mat(const spike_stream* s, const uint64_t* masks, float* out,
                     : rt == 2 ? (nt ? spk::k_stream_mat<2, true> : spk::k_stream_mat<2, false>)
                               : (nt ? spk::k_stream_mat<1, true> : spk::k_stream_mat<1, false>);
     hipLaunchKernelGGL(fn, dim3((unsigned)(slots * row_tiles)), dim3(spk::kColBlock), spk::column_lds(rt, max_K), st,
-                       s->d_ops, s->layout, s->order, s->n_proj, s->n_sets, s->n_tokens, s->N, col_tiles, row_tiles,
+                       s->d_ops, s->order, s->n_proj, s->n_sets, s->n_tokens, s->N, col_tiles, row_tiles,
                        masks, (int)s->mask_stride, out, s->out_stride);
     return true;
 }
@@ -1067,10 +1072,13 @@ int spike_stream_create(const spike_proj_t* projs, int32_t n_proj, int32_t n_set
         delete s;
         return fail(SPIKE_EUNSUPPORTED, "token mask stride too large");
     }
-    for (int j = 0; j < n_proj; ++j)
-        s->order.proj[j] = (uint8_t)j;
+    std::iota(s->order.proj, s->order.proj + n_proj, 0);
     std::stable_sort(s->order.proj, s->order.proj + n_proj,
-                     [&](uint8_t a, uint8_t b) { return s->layout.K[a] > s->layout.K[b]; });
+                     [&](int a, int b) { return s->layout.K[a] > s->layout.K[b]; });
+    for (int i = 0; i < n_proj; ++i) {
+        s->order.K[i] = s->layout.K[s->order.proj[i]];
+        s->order.mask_off[i] = s->layout.mask_off[s->order.proj[i]];
+    }
     s->n_proj = n_proj;
     s->n_sets = n_sets;
     s->n_tokens = n_tokens;

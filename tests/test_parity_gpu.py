@@ -9,6 +9,7 @@ import torch
 import oracle
 from paper_2606_03026_amd import workloads as wl
 from tests.golden.load import load_hand_example
+from tests.launches import kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -687,6 +688,84 @@ def test_stream_matrix_core_form_nontemporal(sp, T):
     for j in (0, 31, 63):
         ref = oracle.spike_forward(p["W"], p["scale"], np.ascontiguousarray(masks[:, j * 256:(j + 1) * 256]), threads=8)
         np.testing.assert_array_equal(bits32(got[:, j * N:(j + 1) * N]), bits32(ref))
+    st.close()
+
+
+# The matrix-core form walks a list of the columns that some token of a tile
+# activates where they are few: no column, one, whole steps of 64 and one more,
+# the longest list of each tile height and one more (all columns are walked
+# then), and every column; K whose words a thread scans one or two of, K = 16384
+# and the longest of 32-token tiles; tokens around the tiles, and weight copies
+# whose tiles are not full.
+@pytest.mark.parametrize("T,n_sets,N,K,active", [
+    (5, 1, 136, 640, 0), (5, 1, 16, 640, 1), (8, 1, 136, 640, 64), (9, 1, 136, 641, 65), (16, 1, 136, 640, 256),
+    (16, 1, 136, 640, 257), (16, 1, 128, 640, 640), (20, 2, 136, 2000, 1408), (20, 2, 136, 2000, 1409), (13, 2, 264, 8193, 700),
+    (9, 1, 24, 16384, 100), (16, 1, 24, 16384, 11136), (16, 1, 24, 16384, 11137), (17, 1, 136, 640, 256), (32, 1, 136, 640, 257),
+    (65, 3, 136, 2000, 1024), (65, 3, 136, 2000, 1025), (32, 1, 24, 16256, 2048), (32, 1, 24, 16256, 2049),
+    (33, 1, 136, 2000, 50), (64, 1, 24, 8192, 300), (64, 1, 24, 8193, 300), (70, 1, 136, 1, 1)])
+def test_stream_listed_columns(sp, T, n_sets, N, K, active):
+    rng = np.random.default_rng([42, 35, T, N, K, active])
+    host = [(rng.integers(-128, 128, (K, N)).astype(np.int8), rng.uniform(-1e-2, 1e-2, N).astype(np.float32)) for _ in range(n_sets)]
+    hs = [sp.spike_proj_create_reserved(dev(W), dev(sc), 1, gather_only=True) for W, sc in host]
+    bits = np.zeros((T, K), bool)
+    cols = rng.choice(K, active, replace=False)
+    bits[:, cols] = rng.random((T, active)) < 0.2
+    for s in range(n_sets):  # every column of the set is active in some token of each 16
+        rows = np.arange(s, T, n_sets)
+        for r0 in range(0, rows.size, 16):
+            tile = rows[r0:r0 + 16]
+            bits[tile[rng.integers(0, tile.size, active)], cols] = True
+    masks = wl.pack_bits(bits)
+    clean = masks.copy()
+    if K % 64:
+        masks[:, -1] |= np.uint64((~((1 << (K % 64)) - 1)) & 0xFFFFFFFFFFFFFFFF)  # junk past K
+    st = sp.spike_stream_create(hs, 1, n_sets, T)
+    flat = torch.full((T * N + 8,), 3.5, device="cuda")
+    dm = dmask(masks)
+    out = flat[:T * N].view(T, N)
+    assert kernels(lambda s: sp.spike_stream_forward(st, dm, out, stream=s))[0].startswith("k_stream_mat<")
+    sp.spike_stream_forward(st, dm, out)
+    torch.cuda.synchronize()
+    assert (flat[T * N:] == 3.5).all()
+    got = out.cpu().numpy()
+    for s, (W, sc) in enumerate(host):
+        ref = oracle.spike_forward(W, sc, np.ascontiguousarray(clean[s::n_sets]), threads=8)
+        np.testing.assert_array_equal(bits32(got[s::n_sets]), bits32(ref))
+    st.close()
+
+
+# One matrix of K x N named by n projections, so that a few bytes stand for many.
+@pytest.mark.parametrize("T,N,K,n,kernel", [
+    (4, 256, 256, 2, "k_stream"), (5, 256, 256, 2, "k_stream_mat<1,0>"), (16, 256, 256, 2, "k_stream_mat<1,0>"),
+    (17, 256, 256, 2, "k_stream_mat<2,0>"), (32, 256, 256, 2, "k_stream_mat<2,0>"), (33, 256, 256, 2, "k_stream_mat<4,0>"),
+    (16, 20, 256, 2, "k_stream"), (8, 272, 8064, 64, "k_stream"), (9, 272, 8064, 64, "k_stream_mat<1,0>"),
+    (16, 1152, 8064, 64, "k_stream_mat<1,1>"), (65, 1152, 8064, 64, "k_stream_mat<4,0>"), (16, 1160, 8064, 64, "k_stream_mat<1,0>"),
+    (64, 16, 8192, 1, "k_stream_mat<4,0>"), (64, 16, 8193, 1, "k_stream_mat<2,0>"), (64, 16, 16256, 1, "k_stream_mat<2,0>"),
+    (64, 16, 16257, 1, "k_stream_mat<1,0>")])
+def test_stream_routes(sp, T, N, K, n, kernel):
+    """The kernel a stream takes, and that a set shape keeps the gather."""
+    W, scale = torch.zeros((K, N), dtype=torch.int8, device="cuda"), torch.ones(N, device="cuda")
+    h = sp.spike_proj_create_reserved(W, scale, 1, gather_only=True)
+    st = sp.spike_stream_create([h] * n, n, 1, T)
+    masks = torch.zeros((T, n * wl.words_per_row(K)), dtype=torch.int64, device="cuda")
+    out = torch.zeros((T, n * N), device="cuda")
+    route = lambda: kernels(lambda s: sp.spike_stream_forward(st, masks, out, stream=s))  # noqa: E731
+    assert route() == [kernel]
+    for key, value, default in ((sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(1, 64, 4, 256), 0),):
+        sp.spike_stream_tune(st, key, value)
+        assert route() == ["k_stream"]
+        sp.spike_stream_tune(st, key, default)
+        assert route() == [kernel]
+    st.close()
+    h.close()
+
+
+def test_stream_unaligned_weights_gather(sp):
+    W = torch.zeros(256 * 256 + 4, dtype=torch.int8, device="cuda")[4:].view(256, 256)
+    h = sp.spike_proj_create_reserved(W, torch.ones(256, device="cuda"), 1, gather_only=True)
+    st = sp.spike_stream_create([h], 1, 1, 16)
+    masks, out = torch.zeros((16, 4), dtype=torch.int64, device="cuda"), torch.zeros((16, 256), device="cuda")
+    assert kernels(lambda s: sp.spike_stream_forward(st, masks, out, stream=s)) == ["k_stream"]
     st.close()
 
 
