@@ -274,13 +274,15 @@ int spike_stack_forward_fused(const spike_proj_t *projs, int32_t n_proj, const u
  * rows: where 9 or more share a copy (5 where the weights of all copies take up
  * to 128 MiB), N % 8 == 0 and the weights are 8-byte aligned, they run on the
  * matrix cores straight from the column-major weights, reading the columns that
- * some token of a tile activates; otherwise, or with SPIKE_TUNE_SHAPE set,
+ * some token of a tile activates; otherwise, or with a launch-shape control set,
  * each token gathers its active columns.  Results are identical. */
 int spike_stream_create(const spike_proj_t *projs, int32_t n_proj, int32_t n_sets, int32_t n_tokens,
                         spike_stream_t *out_stream);
 int spike_stream_forward(spike_stream_t s, const uint64_t *masks, float *out, void *stream);
-/* Launch-shape controls of a stream (SPIKE_TUNE_SHAPE, SPIKE_TUNE_TILES_PER_UNIT
- * as for spike_proj_tune); results never depend on them. */
+/* Launch-shape controls of a stream's gather (SPIKE_TUNE_SHAPE,
+ * SPIKE_TUNE_TILES_PER_UNIT, SPIKE_TUNE_XCD_SPREAD as for spike_proj_tune); with
+ * one of them away from its default (0, 1, 8) the gather runs.  Results never
+ * depend on them. */
 int spike_stream_tune(spike_stream_t s, int32_t key, int32_t value);
 int spike_stream_destroy(spike_stream_t s);
 

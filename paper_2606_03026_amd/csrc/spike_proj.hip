@@ -189,7 +189,8 @@ struct spike_stream {
     spk::StreamOperands* d_ops = nullptr;  // device operand table [n_sets][n_proj]
     spk::StreamLayout layout{};
     spk::ColumnOrder order{};     // projections by falling K, for the matrix-core form
-    bool shape_pinned = false;    // a launch shape was set: the gather runs
+    bool shape_pinned = false;    // a launch shape was set
+    bool gather_pinned() const { return shape_pinned || tiles_per_unit != 1 || xcd_spread != 8; }  // a control of the gather was set
     bool mat_ok = false;          // sizes and alignment allow the matrix-core form
     int64_t set_bytes = 0;        // weight bytes of one set
     std::vector<const void*> weights;  // to re-check alignment when the shape changes
@@ -248,7 +249,7 @@ bool launch_stream_mat(const spike_stream* s, const uint64_t* masks, float* out,
     const int sets = std::min(s->n_sets, s->n_tokens);
     const int rows = (s->n_tokens + sets - 1) / sets;  // of the fullest weight copy
     const int64_t bytes = s->set_bytes * sets;
-    if (s->shape_pinned || !s->mat_ok || rows < (bytes > kStreamMatSmallBytes ? kStreamMatMinRows : kStreamMatSmallMinRows))
+    if (s->gather_pinned() || !s->mat_ok || rows < (bytes > kStreamMatSmallBytes ? kStreamMatMinRows : kStreamMatSmallMinRows))
         return false;
     int rt = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
     const int max_K = s->order.K[0];

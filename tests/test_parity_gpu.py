@@ -743,7 +743,7 @@ def test_stream_listed_columns(sp, T, n_sets, N, K, active):
     (64, 16, 8192, 1, "k_stream_mat<4,0>"), (64, 16, 8193, 1, "k_stream_mat<2,0>"), (64, 16, 16256, 1, "k_stream_mat<2,0>"),
     (64, 16, 16257, 1, "k_stream_mat<1,0>")])
 def test_stream_routes(sp, T, N, K, n, kernel):
-    """The kernel a stream takes, and that a set shape keeps the gather."""
+    """The kernel a stream takes, and that every control of the gather keeps the gather."""
     W, scale = torch.zeros((K, N), dtype=torch.int8, device="cuda"), torch.ones(N, device="cuda")
     h = sp.spike_proj_create_reserved(W, scale, 1, gather_only=True)
     st = sp.spike_stream_create([h] * n, n, 1, T)
@@ -751,7 +751,8 @@ def test_stream_routes(sp, T, N, K, n, kernel):
     out = torch.zeros((T, n * N), device="cuda")
     route = lambda: kernels(lambda s: sp.spike_stream_forward(st, masks, out, stream=s))  # noqa: E731
     assert route() == [kernel]
-    for key, value, default in ((sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(1, 64, 4, 256), 0),):
+    for key, value, default in ((sp.SPIKE_TUNE_TILES_PER_UNIT, 2, 1), (sp.SPIKE_TUNE_XCD_SPREAD, 1, 8),
+                                (sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(1, 64, 4, 256), 0)):
         sp.spike_stream_tune(st, key, value)
         assert route() == ["k_stream"]
         sp.spike_stream_tune(st, key, default)
