@@ -664,29 +664,31 @@ def test_stream_matrix_core_form(sp, T, n_sets, N, Ks, offset):
     st.close()
 
 
-@pytest.mark.parametrize("T", [10, 31, 40])
-def test_stream_matrix_core_form_nontemporal(sp, T):
+@pytest.mark.parametrize("T,kernel", [(10, "k_stream_mat<1,1>"), (31, "k_stream_mat<2,1>"), (40, "k_stream_mat<4,1>")])
+def test_stream_matrix_core_form_nontemporal(sp, T, kernel):
     """More weight bytes than the rule for nontemporal loads (one matrix named
     by 64 projections), at each row tile: three projections against the
     oracle, all against the gather."""
-    K, N, n = 16384, 640, 64
+    K, N, n = 8064, 1152, 64
     p = wl.small_problem(K, N, 1, 0.1, seed=12)
     h = sp.spike_proj_create_reserved(dev(p["W"]), dev(p["scale"]), 1, gather_only=True)
     rng = np.random.default_rng([42, 34, T])
-    masks = np.concatenate([wl.pack_bits(rng.random((T, K)) < 0.02) for _ in range(n)], axis=1)
+    masks = np.concatenate([wl.pack_bits(rng.random((T, K)) < (0.02 if j % 2 else 0.2)) for j in range(n)], axis=1)
     st = sp.spike_stream_create([h] * n, n, 1, T)
     outs = []
     for pinned in (False, True):
         if pinned:
             sp.spike_stream_tune(st, sp.SPIKE_TUNE_SHAPE, sp.SPIKE_SHAPE(16, 32, 4, 256, True))
         out = torch.full((T, n * N), float("nan"), device="cuda")
-        sp.spike_stream_forward(st, dmask(masks), out)
+        dm = dmask(masks)
+        assert kernels(lambda s: sp.spike_stream_forward(st, dm, out, stream=s)) == ["k_stream" if pinned else kernel]
+        sp.spike_stream_forward(st, dm, out)
         torch.cuda.synchronize()
         outs.append(out)
     assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
-    got = outs[0].cpu().numpy()
+    got, words = outs[0].cpu().numpy(), wl.words_per_row(K)
     for j in (0, 31, 63):
-        ref = oracle.spike_forward(p["W"], p["scale"], np.ascontiguousarray(masks[:, j * 256:(j + 1) * 256]), threads=8)
+        ref = oracle.spike_forward(p["W"], p["scale"], np.ascontiguousarray(masks[:, j * words:(j + 1) * words]), threads=8)
         np.testing.assert_array_equal(bits32(got[:, j * N:(j + 1) * N]), bits32(ref))
     st.close()
 
