@@ -198,7 +198,6 @@ template <int RT, class RowOf>
 __device__ inline void finish_column_tile(const mf_i32x4 (&acc)[RT][8], int wave, int l, int n0, int N,
                                           const float* scale, uint8_t* lds, RowOf row_of)
 {
-    const f32x4 s4 = *reinterpret_cast<const f32x4*>(scale + 4 * (l % 32));
     constexpr int kPairs = RT;
     constexpr int kRound = column_round(RT);
     i32x4* part = reinterpret_cast<i32x4*>(lds);  // [4 kRound places][kColWaves sources][64 lanes][2]
@@ -219,6 +218,7 @@ __device__ inline void finish_column_tile(const mf_i32x4 (&acc)[RT][8], int wave
                         i32x4{acc[rt][4 * h][j], acc[rt][4 * h + 1][j], acc[rt][4 * h + 2][j], acc[rt][4 * h + 3][j]};
                 }
         __syncthreads();
+        const f32x4 s4 = *reinterpret_cast<const f32x4*>(scale + 4 * (l % 32));  // written before the barriers
         constexpr int kEach = 8 * kRound / kColWaves;  // half places of a wave
 #pragma unroll
         for (int k = 0; k < kEach; ++k) {
