@@ -233,8 +233,9 @@ __device__ __attribute__((always_inline)) inline void mfma_tile(const int8_t* __
         }
     }
 
-    // Every wave has at least one k-step (the plan requires KW <= wpr).
-    // Loads are unconditional (a step past the wave's last reads out of
+    // Every wave has at least one k-step (the plan requires KW <= wpr), except
+    // in launches of several projections, where waves past a short one's last
+    // step add zeros.  Loads are unconditional (a step past the wave's last reads out of
     // range, see load_w): a conditional load would turn its registers into
     // phis that the compiler fills with copies.
     u32x4 wbuf[D][CS];
@@ -289,7 +290,7 @@ __device__ __attribute__((always_inline)) inline void mfma_tile(const int8_t* __
     // 16-bit LDS read per row subtile), and the A-operands built from them.
     const uint16_t* xs16 = reinterpret_cast<const uint16_t*>(xs);
     auto read_bits = [&](int i, uint32_t (&b)[RT]) {
-        const int s = wave + i * KW;
+        const int s = min(wave + i * KW, wpr - 1);  // a wave without steps reads, and multiplies, nothing of its own
 #pragma unroll
         for (int ms = 0; ms < RT; ++ms)
             b[ms] = xs16[((16 * ms + c) * pitch + s) * 4 + q];
@@ -853,18 +854,17 @@ inline MfmaPlan mfma_plan(int K, int N, int B, int rt_req, int cs_req, int kw_re
     return p;
 }
 
-// A ring plan (any k-step count) for a launch whose projections all have
-// at least min_wpr k-steps: an instantiated ring plan with a channel-set
-// count dividing N / 16 and at most min_wpr waves, preferring p's row tile,
-// then p's channel sets, then the most waves up to p's, then p's depth.
-// Returns false if none.
-inline bool mfma_ring_plan(MfmaPlan& p, int min_wpr, int N)
+// A ring plan (any k-step count) for a launch of several projections: an
+// instantiated ring plan with a channel-set count dividing N / 16 and at most
+// max_kw waves, preferring p's row tile, then p's channel sets, then the most
+// waves up to p's, then p's depth.  Returns false if none.
+inline bool mfma_ring_plan(MfmaPlan& p, int max_kw, int N)
 {
     const int sets = N / 16;
     MfmaPlan best{};
     int best_score = -1;
 #define SPK_RING(RT, CS, KW, D, PRE)                                                                 \
-    if (!PRE && KW <= min_wpr && sets % CS == 0) {                                                  \
+    if (!PRE && KW <= max_kw && sets % CS == 0) {                                                  \
         const int score = (RT == p.rt ? 1 << 24 : 0) + (CS == p.cs ? 1 << 20 : 0) +                 \
                           (KW <= p.kw ? KW << 8 : 0) + (D == p.d ? 1 : 0);                          \
         if (score > best_score) {                                                                    \
@@ -953,8 +953,8 @@ inline int mfma_plan_codes(int32_t* codes, int cap)
 }
 
 // Is the plan instantiated and runnable for this shape?  Returns 0 or a
-// message.
-inline const char* mfma_plan_check(const MfmaPlan& p, int K, int N)
+// message.  idle_waves: waves may be left without k-steps (ring plans only).
+inline const char* mfma_plan_check(const MfmaPlan& p, int K, int N, bool idle_waves = false)
 {
     const int wpr = (K + 63) / 64;
     if (!mfma_instantiated(p))
@@ -963,7 +963,7 @@ inline const char* mfma_plan_check(const MfmaPlan& p, int K, int N)
         return "N / 16 is not a multiple of the tile's channel sets";
     if (mfma_lds_bytes(p.rt, p.cs, wpr) > kMfmaMaxLds)
         return "the tile's staged spike words exceed the LDS budget";
-    if (wpr < p.kw)
+    if (wpr < p.kw && !idle_waves)
         return "fewer k-steps than waves";
     if (p.preload && (wpr + p.kw - 1) / p.kw > p.d)
         return "more k-steps per wave than the preload depth";

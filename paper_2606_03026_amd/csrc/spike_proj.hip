@@ -449,12 +449,12 @@ spk::MfmaPlan mfma_plan_of(const spike_proj* h, int32_t B)
 // Why the matrix-core path cannot serve B rows of a K x N projection with
 // plan p (null: it can).  The kernel addresses the spike words of its row
 // tiles (including the padding rows of the last one) with 31-bit offsets.
-const char* mfma_refusal(int32_t K, int32_t N, bool has_copy, int32_t B, const spk::MfmaPlan& p)
+const char* mfma_refusal(int32_t K, int32_t N, bool has_copy, int32_t B, const spk::MfmaPlan& p, bool idle_waves = false)
 {
     if (!has_copy)
         return "the handle has no matrix-core copy of W (it needs N % 16 == 0, fewer than 2^31 packed bytes, "
                "a reserved batch of at least the matrix-core minimum and the memory for the copy)";
-    if (const char* why = spk::mfma_plan_check(p, K, N))
+    if (const char* why = spk::mfma_plan_check(p, K, N, idle_waves))
         return why;
     const int64_t tile = 16ll * p.rt;
     const int64_t rows = ((int64_t)B + tile - 1) / tile * tile;
@@ -608,6 +608,8 @@ int static_scratch(int dev, hipStream_t st, uint32_t** out)
     return SPIKE_OK;
 }
 
+constexpr int kFusedMinTiles = 256;  // compute units
+
 // The projections of spike_stack_forward_fused in one launch (arguments
 // checked); SPIKE_EUNSUPPORTED where they cannot run together.
 int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* masks, int32_t B, float* out, void* stream)
@@ -625,13 +627,21 @@ int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* mas
     }
     if (int rc = check_device(projs[0]->device))
         return rc;
-    // one ring plan for all items, chosen for the shortest K (every wave needs a k-step)
+    // One ring plan for all items, with waves for the longest K: a wave past a
+    // short projection's last k-step adds zeros.  (A plan cut to the shortest K
+    // ran K = 16384 beside K = 64, 512 channels, in single waves: one row 28.0 us
+    // against 8.7 for the two launches, now 7.3; 6144 beside 64, 1536 channels, 32
+    // rows 41 against 9.7, now 6.1.)
     // Tiles of up to 64 rows by 48 channels, two k-steps in flight per wave;
     // 8 waves for 64-row tiles (measured on the 64-row decode stack, 1408
     // workgroups over 44 projections: 49 us per step against 57 us with 16
-    // waves, 53 with 4), 16 for the narrower tiles of smaller batches; the
-    // first handle's matrix-core tuning knobs override it for the whole
-    // launch.
+    // waves, 53 with 4), 16 for the narrower tiles of smaller batches.  Few
+    // projections take shorter tiles, then narrower ones, until every compute unit
+    // has a tile: 2 x 6144 -> 1536 at 64 rows 7.7 us against 10.9, 1536 -> 1536 and
+    // 6144 -> 1536 at 64 rows 7.3 against 10.6 (two launches 9.4), at one row 5.5
+    // against 7.1; asking for 1.5 or 2 tiles a unit costs more than it gives (8
+    // projections of the 1536-wide stack at 32 rows 16.6 us against 13.6).  The
+    // first handle's matrix-core tuning knobs override it for the whole launch.
     const spike_proj* h0 = projs[0];
     const int sets = N / spk::kMfmaNAlign;
     spk::MfmaPlan p{};
@@ -647,13 +657,26 @@ int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* mas
         p.kw = h0->mfma_waves;
     if (h0->mfma_depth > 0)
         p.d = h0->mfma_depth;
-    if (N % spk::kMfmaNAlign != 0 || !spk::mfma_ring_plan(p, (int)words_per_row(min_K), N))
+    auto too_few = [&] {
+        return (int64_t)n_proj * (sets / p.cs) * ((B + 16 * p.rt - 1) / (16 * p.rt)) < kFusedMinTiles;
+    };
+    for (; h0->mfma_row_tile == 0 && p.rt > 1 && too_few(); p.rt /= 2)
+        p.kw = h0->mfma_waves > 0 ? h0->mfma_waves : 16;
+    while (h0->mfma_col_sets == 0 && p.cs > 1 && too_few())
+        p.cs = 1;
+    const spk::MfmaPlan want = p;
+    bool found = N % spk::kMfmaNAlign == 0 && spk::mfma_ring_plan(p, max_wpr, N);
+    if (found && spk::mfma_lds_bytes(p.rt, p.cs, max_wpr) > spk::kMfmaMaxLds) {
+        p = want;  // fewer waves may come with narrower tiles
+        found = spk::mfma_ring_plan(p, (int)words_per_row(min_K), N);
+    }
+    if (!found)
         return fail(SPIKE_EUNSUPPORTED, "no matrix-core plan serves N = %d, K >= %d, B = %d in one launch", N, min_K, B);
     spk::MfmaItems items{};
     int64_t moff = 0, ooff = 0;
     for (int j = 0; j < n_proj; ++j) {
         const spike_proj* h = projs[j];
-        if (const char* why = mfma_refusal(h->K, N, h->packed != nullptr, B, p))
+        if (const char* why = mfma_refusal(h->K, N, h->packed != nullptr, B, p, true))
             return fail(SPIKE_EUNSUPPORTED, "projection %d (K = %d) cannot run on the matrix cores with B = %d: %s", j,
                         h->K, B, why);
         items.P[j] = h->packed;

@@ -363,6 +363,40 @@ def test_stack_forward_routes(sp, B, variant):
     np.testing.assert_array_equal(bits32(out.cpu().numpy()), bits32(ref))
 
 
+# Projections of unlike K in one launch: waves for the longest K, so that the
+# shorter ones leave waves idle (down to one word beside 16 waves), in the order
+# of the call and reversed; tiles narrowed while compute units are left over;
+# and the one shape whose tiles fit LDS only with the plan of the shortest K.
+@pytest.mark.parametrize("B,N,Ks,kernel", [
+    (1, 512, (64, 16384), "k_mfma_items<1,1,16,2>"), (8, 512, (16384, 1, 65), "k_mfma_items<1,1,16,2>"),
+    (32, 1536, (64, 6144), "k_mfma_items<1,1,16,2>"), (33, 1536, (6144, 64, 700, 1), "k_mfma_items<2,3,16,2>"),
+    (64, 1536, (64, 6144) * 6, "k_mfma_items<4,3,8,2>"), (64, 512, (1, 1000) * 20, "k_mfma_items<4,2,8,4>"),
+    (17, 80, (33, 129, 1025), "k_mfma_items<1,1,16,2>"), (64, 8192, (64, 7616), "k_mfma_items<4,1,1,2>")])
+def test_stack_of_unlike_k(sp, B, N, Ks, kernel):
+    rng = np.random.default_rng([42, 36, B, N, len(Ks)])
+    host = [(rng.integers(-127, 128, (K, N)).astype(np.int8), rng.uniform(1e-3, 1e-2, N).astype(np.float32)) for K in Ks]
+    hs = [sp.spike_proj_create_reserved(dev(W), dev(s), B) for W, s in host]
+    masks, clean = [], []
+    for K in Ks:
+        m = wl.pack_bits(rng.random((B, K)) < 0.1)
+        clean.append(m.copy())
+        if K % 64:
+            m[:, -1] |= np.uint64((~((1 << (K % 64)) - 1)) & 0xFFFFFFFFFFFFFFFF)  # junk past K
+        masks.append(m)
+    dm = dmask(np.concatenate([m.ravel() for m in masks]))
+    n_out = B * N * len(Ks)
+    flat = torch.full((n_out + 8,), 3.5, device="cuda")
+    for fn in (sp.spike_stack_forward, sp.spike_stack_forward_fused):
+        assert kernels(lambda s: fn(hs, dm, B, flat[:n_out], stream=s)) == [kernel]
+        flat.fill_(3.5)
+        fn(hs, dm, B, flat[:n_out])
+        torch.cuda.synchronize()
+        assert (flat[n_out:] == 3.5).all()
+        got = flat[:n_out].cpu().numpy().reshape(len(Ks), B, N)
+        for i, ((W, s), m) in enumerate(zip(host, clean)):
+            np.testing.assert_array_equal(bits32(got[i]), bits32(oracle.spike_forward(W, s, m, threads=8)), err_msg=f"item {i}")
+
+
 def test_batch_zero_is_a_noop(sp):
     p = wl.small_problem(100, 64, 1, 0.5)
     h, *_ = make(sp, p["W"], p["scale"])
