@@ -257,9 +257,10 @@ int spike_stack_forward(const spike_proj_t *projs, int32_t n_proj, const uint64_
  * (a reserved batch of at least the matrix-core minimum), B rows reserved;
  * at most 64 projections.  Returns SPIKE_EUNSUPPORTED where these do not
  * hold (spike_stack_forward then serves the call).  Results are identical
- * to spike_stack_forward's.  For up to 8 rows of enough weight bytes the
- * launch reads the columns of W that any row activates instead of the packed
- * copies (W 8-byte aligned, every K <= 16384). */
+ * to spike_stack_forward's.  For up to 8 rows of enough weight bytes (W 8-byte
+ * aligned, every K <= 16384) the launch reads the columns of W that any row
+ * activates instead of the packed copies, except where its rows activate most
+ * columns. */
 int spike_stack_forward_fused(const spike_proj_t *projs, int32_t n_proj, const uint64_t *masks, int32_t B,
                               float *out, void *stream);
 

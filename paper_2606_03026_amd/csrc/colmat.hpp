@@ -173,15 +173,25 @@ __device__ __attribute__((always_inline)) inline void column_products(const mf_i
     }
 }
 
-// Byte b of x holds eight columns of row b; afterwards byte i holds the rows of column i.
-__device__ inline uint64_t transpose_bits(uint64_t x)
+// Eight rows of 32 columns; afterwards byte b of d[i] holds the eight rows of
+// column 8 b + i (four 8 x 8 bit-matrix transposes side by side, in three rounds
+// of exchanged half blocks: Warren, Hacker's Delight, section 7-3).
+__device__ inline void transpose_rows(uint32_t (&d)[8])
 {
-    uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
-    x ^= t ^ (t << 7);
-    t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
-    x ^= t ^ (t << 14);
-    t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
-    return x ^ t ^ (t << 28);
+    auto exchange = [](uint32_t& x, uint32_t& y, int s, uint32_t low) {
+        const uint32_t a = (x & low) | ((y << s) & ~low), b = ((x >> s) & low) | (y & ~low);
+        x = a;
+        y = b;
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        exchange(d[r], d[r + 4], 4, 0x0f0f0f0fu);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        exchange(d[r / 2 * 4 + r % 2], d[r / 2 * 4 + r % 2 + 2], 2, 0x33333333u);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        exchange(d[2 * r], d[2 * r + 1], 1, 0x55555555u);
 }
 
 // The sums of a workgroup's waves, scaled and stored.  Register j of lane
@@ -477,29 +487,40 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(RT ==
 }
 
 // ---------------------------------------------------------------------------
-// The same contraction over the columns that are active in any of up to 8
-// rows: at a rate of 0.1 seven rows touch half the columns, one row a tenth,
-// and the others' weights are not read.
+// The same contraction for up to 8 rows of several projections at once: at a
+// rate of 0.1 seven rows touch half the columns, one row a tenth, and the
+// others' weights are not read.
 //
-// The union of the rows' spikes becomes a list of columns in LDS with a byte
-// per column holding which rows are active there (an 8 x 8 bit transpose of
-// the rows' bytes).  A step is 64 entries of the list, lane 16 q + c taking
-// entries 16 q .. 16 q + 15: its weight loads go to those columns, and the
-// spike operand of row c is bit c of the entries' row bytes, a shift and an
-// AND per four columns.  Entries past the list name column K, whose weights
-// read as zero.  Everything else is as above, but with 8 waves to a workgroup.
+// The union of the rows' spikes is counted; up to 5/8 of the columns (25/32 where
+// the packed copy comes from HBM at every step) it becomes a list in LDS with a byte per column holding which rows are active there (8 x
+// 8 bit transposes of the rows' bytes).  A step is 64 entries of the list, lane
+// 16 q + c taking entries 16 q .. 16 q + 15: its weight loads go to those
+// columns, and the spike operand of row c is bit c of the entries' row bytes, a
+// shift and an AND per four columns.  Entries past the list name column K, whose
+// weights read as zero.  Above that the tile reads all columns, from the packed
+// copy (layout in mfma.hpp), whose 1 KB pieces stream faster than scattered
+// columns.  Sums and stores are as above, but with 8 waves to a workgroup.
 //
-// What bounds it is the random 128-byte reads: 7 rows of the 44-projection
-// stack, 143 MB of active columns, take 38 us, of which 8 are the launch, the
+// What bounds the list is the random 128-byte reads: 7 rows of the 44-projection
+// stack, 143 MB of active columns, take 37 us, of which 8 are the launch, the
 // lists and the sums (a timing copy with one step per wave); 4 waves a
 // workgroup take 40, and wider tiles (2 or 3 x 128 channels sharing a list)
-// 44 and 50: half as many workgroups leave compute units idle.
+// 44 and 50: half as many workgroups leave compute units idle.  Where the lines
+// lie, with a hot twentieth of the columns, listed against packed tiles against
+// a launch of packed tiles alone, which does not count first: 248 MiB, 6 rows at
+// 0.2 (0.75 active) 50.4 / 53.9 / 51.7 us, 7 rows (0.79) 51.8 / 53.9 / 52, 4 rows at
+// 0.4 (0.88) 60 / 54 / 51, 8 rows at 0.4 60 / 54 / 52; 110 MiB, 4 rows at 0.2 (0.61)
+// 26.6 / 26.5 / 25.0, 5 rows (0.69) 28.4 / 26.6 / 25.2, 8 rows at 0.4 35 / 27 / 25; 62
+// MiB, 4 rows at 0.2 18.9 / 19.5 / 18.2, 3 rows at 0.4 (0.79) 22.5 / 19.4 / 18.1; 52
+// MiB, 1040 wide, 2 rows at 0.4 (0.66) 20.4 / 17.3 / 16.2.
 // ---------------------------------------------------------------------------
 constexpr int kActiveMaxRows = 8;
 constexpr int kActiveMaxK = 64 * kMaxSliceWords;
 constexpr int kActiveWaves = 8;
 constexpr int kActiveBlock = 64 * kActiveWaves;
 constexpr int kActiveStep = 64;
+constexpr int kActiveHalf = 16 * kActiveBlock;  // columns that the threads take 16 each
+static_assert(kActiveMaxK <= 2 * kActiveHalf);
 // list (16-bit columns) and row bytes, padded by the step read past the end;
 // later the waves' sums of the 8 rows
 inline int active_lds(int K)
@@ -509,9 +530,11 @@ inline int active_lds(int K)
 }
 
 // One workgroup: n_rows rows (spike row r at byte mask0 + r * mask_pitch of
-// the resource mres) against channels n0 .. n0 + 127 of W.
-template <bool NT, class RowOf>
-__device__ __attribute__((always_inline)) inline void active_tile(const int8_t* W, const float* scale, int K, int N, int n0,
+// the resource mres) against channels n0 .. n0 + 127 of W or its packed copy P.
+// NT, NTP: loads of W, of P marked nontemporal.
+template <bool NT, bool NTP, class RowOf>
+__device__ __attribute__((always_inline)) inline void active_tile(const int8_t* W, const int8_t* P, const float* scale, int K,
+                                                                  int N, int n0,
                                                                   __amdgpu_buffer_rsrc_t mres, uint32_t mask0,
                                                                   uint32_t mask_pitch, int n_rows, uint8_t* lds,
                                                                   RowOf row_of)
@@ -529,91 +552,121 @@ __device__ __attribute__((always_inline)) inline void active_tile(const int8_t* 
     if (threadIdx.x < kColChannels)
         scales[threadIdx.x] = n0 + (int)threadIdx.x < N ? scale[n0 + threadIdx.x] : 0.0f;
 
-    // Compaction, 16 columns per thread (8192 per pass).
-    int cnt = 0;
-    for (int k0 = 0; k0 < K; k0 += 16 * kActiveBlock) {
-        const int kt = k0 + 16 * (int)threadIdx.x;  // this thread's first column
-        uint32_t d[kActiveMaxRows];
+    // The rows' spikes at this thread's columns: kt .. kt + 15, and as many from
+    // kActiveHalf on (the upper halves of d).
+    const int kt = 16 * (int)threadIdx.x;
+    uint32_t d[kActiveMaxRows], any = 0;
 #pragma unroll
-        for (int r = 0; r < kActiveMaxRows; ++r)
-            d[r] = __builtin_amdgcn_raw_buffer_load_b16(
-                mres, r < n_rows && kt < K ? mask0 + r * mask_pitch + (uint32_t)kt / 8 : kOutOfRange, 0, 0);
-        const uint32_t valid = K - kt >= 16 ? 0xffffu : kt < K ? (1u << (K - kt)) - 1u : 0u;
-        uint64_t byte_rows[2] = {0, 0};
-        uint32_t any = 0;
-#pragma unroll
-        for (int r = 0; r < kActiveMaxRows; ++r) {
-            d[r] &= valid;
-            any |= d[r];
-            byte_rows[0] |= (uint64_t)(d[r] & 0xffu) << (8 * r);
-            byte_rows[1] |= (uint64_t)(d[r] >> 8) << (8 * r);
-        }
-        byte_rows[0] = transpose_bits(byte_rows[0]);
-        byte_rows[1] = transpose_bits(byte_rows[1]);
-        const int mine = __popc(any), incl = wave_scan(mine);
-        if (k0 > 0)
-            __syncthreads();  // the totals of the pass before have been read
-        if (l == 63)
-            wave_total[wave] = incl;
-        __syncthreads();
-        int pos = cnt + incl - mine;
-#pragma unroll
-        for (int w = 0; w < kActiveWaves; ++w) {
-            const int wt = wave_total[w];
-            pos += w < wave ? wt : 0;
-            cnt += wt;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t rb = (uint32_t)(byte_rows[i / 8] >> (8 * (i % 8))) & 0xffu;
-            if (rb) {
-                list[pos] = (uint16_t)(kt + i);
-                rows[pos] = (uint8_t)rb;
-                ++pos;
-            }
-        }
+    for (int r = 0; r < kActiveMaxRows; ++r) {
+        const uint32_t at = mask0 + r * mask_pitch + (uint32_t)kt / 8;
+        d[r] = __builtin_amdgcn_raw_buffer_load_b16(mres, r < n_rows && kt < K ? at : kOutOfRange, 0, 0);
+        if (K > kActiveHalf)
+            d[r] |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(
+                        mres, r < n_rows && kActiveHalf + kt < K ? at + kActiveHalf / 8 : kOutOfRange, 0, 0) << 16;
+        any |= d[r];
     }
-    const int n_steps = (cnt + kActiveStep - 1) / kActiveStep;
-    for (int e = cnt + (int)threadIdx.x; e < (n_steps + 1) * kActiveStep; e += kActiveBlock) {
-        list[e] = (uint16_t)K;
-        rows[e] = 0;
-    }
+    auto valid = [](int left) { return left >= 16 ? 0xffffu : left > 0 ? (1u << left) - 1u : 0u; };
+    any &= valid(K - kt) | valid(K - kActiveHalf - kt) << 16;
+    const int mine = __popc(any), incl = wave_scan(mine);
+    if (l == 63)
+        wave_total[wave] = incl;
     __syncthreads();
-
-    const __amdgpu_buffer_rsrc_t wres = weight_resource(W, (int64_t)K * N);
-    const uint32_t lane_off = n0 + 8 * c < N ? (uint32_t)(n0 + 8 * c) : kOutOfRange;  // channels past N: no request
-    auto load_weights = [&](int s, u32x2 (&w)[16]) {
-        const u32x4* at = reinterpret_cast<const u32x4*>(list + min(s, n_steps) * kActiveStep + 16 * q);
-        const u32x4 two[2] = {at[0], at[1]};
+    int pos = incl - mine, cnt = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t pair = two[i / 8][i % 8 / 2];
-            const uint32_t col = i % 2 ? pair >> 16 : pair & 0xffffu;
-            w[i] = __builtin_amdgcn_raw_buffer_load_b64(wres, __umul24(col, N) + lane_off, 0, NT ? 2 : 0);  // K * N < 2^31
-        }
-    };
+    for (int w = 0; w < kActiveWaves; ++w) {
+        pos += w < wave ? wave_total[w] : 0;
+        cnt += wave_total[w];
+    }
     mf_i32x4 acc[1][8];
 #pragma unroll
     for (int t = 0; t < 8; ++t)
         acc[0][t] = mf_i32x4{0, 0, 0, 0};
-    auto products = [&](int s, const u32x2 (&w)[16]) {
-        const u32x4 rb = *reinterpret_cast<const u32x4*>(rows + min(s, n_steps) * kActiveStep + 16 * q);
-        mf_i32x4 a[1];
+    const bool listed = cnt <= (NTP ? K * 25 / 32 : K * 5 / 8);  // the whole workgroup
+    if (listed) {
+        transpose_rows(d);
+        auto add = [&](int half) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            a[0][i] = (int32_t)((rb[i] >> c) & 0x01010101u);  // rows 8 .. 15 are not stored
-        column_products<1>(a, w, acc);
-    };
-    u32x2 w0[16], w1[16];
-    load_weights(wave, w0);
-    load_weights(wave + kActiveWaves, w1);
-    for (int s = wave; s < n_steps; s += 2 * kActiveWaves) {
-        products(s, w0);
-        load_weights(s + 2 * kActiveWaves, w0);
-        __builtin_amdgcn_sched_barrier(0);
-        products(s + kActiveWaves, w1);
-        load_weights(s + 3 * kActiveWaves, w1);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 16; ++i)
+                if (any >> (16 * half + i) & 1) {
+                    list[pos] = (uint16_t)(kt + half * kActiveHalf + i);
+                    rows[pos] = (uint8_t)(d[i % 8] >> (16 * half + i / 8 * 8));
+                    ++pos;
+                }
+        };
+        add(0);
+        if (K > kActiveHalf)
+            add(1);
+        const int n_steps = (cnt + kActiveStep - 1) / kActiveStep;
+        for (int e = cnt + (int)threadIdx.x; e < (n_steps + 1) * kActiveStep; e += kActiveBlock) {
+            list[e] = (uint16_t)K;
+            rows[e] = 0;
+        }
+        __syncthreads();
+
+        const __amdgpu_buffer_rsrc_t wres = weight_resource(W, (int64_t)K * N);
+        const uint32_t lane_off = n0 + 8 * c < N ? (uint32_t)(n0 + 8 * c) : kOutOfRange;  // channels past N: no request
+        auto load_weights = [&](int s, u32x2 (&w)[16]) {
+            const u32x4* at = reinterpret_cast<const u32x4*>(list + min(s, n_steps) * kActiveStep + 16 * q);
+            const u32x4 two[2] = {at[0], at[1]};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t pair = two[i / 8][i % 8 / 2];
+                const uint32_t col = i % 2 ? pair >> 16 : pair & 0xffffu;
+                w[i] = __builtin_amdgcn_raw_buffer_load_b64(wres, __umul24(col, N) + lane_off, 0, NT ? 2 : 0);  // K * N < 2^31
+            }
+        };
+        auto products = [&](int s, const u32x2 (&w)[16]) {
+            const u32x4 rb = *reinterpret_cast<const u32x4*>(rows + min(s, n_steps) * kActiveStep + 16 * q);
+            mf_i32x4 a[1];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                a[0][i] = (int32_t)((rb[i] >> c) & 0x01010101u);  // rows 8 .. 15 are not stored
+            column_products<1>(a, w, acc);
+        };
+        u32x2 w0[16], w1[16];
+        load_weights(wave, w0);
+        load_weights(wave + kActiveWaves, w1);
+        for (int s = wave; s < n_steps; s += 2 * kActiveWaves) {
+            products(s, w0);
+            load_weights(s + 2 * kActiveWaves, w0);
+            __builtin_amdgcn_sched_barrier(0);
+            products(s + kActiveWaves, w1);
+            load_weights(s + 3 * kActiveWaves, w1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        // All columns, from the packed copy: k-step s of channel set t is 1 KB,
+        // lane 16 q + c holding 16 columns of channel 16 t + c.
+        const int wpr = (K + 63) / 64, sets = N / 16, set0 = n0 / 16;
+        const int records = sets * wpr * kMfmaSetStepBytes;
+        const __amdgpu_buffer_rsrc_t pres = weight_resource(P, records);
+        auto load_packed = [&](int s, u32x4 (&w)[8], uint32_t& bits) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                w[t] = __builtin_amdgcn_raw_buffer_load_b128(
+                    pres, 16 * l, s < wpr && set0 + t < sets ? ((set0 + t) * wpr + s) * kMfmaSetStepBytes : records, NTP ? 2 : 0);
+            bits = __builtin_amdgcn_raw_buffer_load_b16(
+                mres, c < n_rows && s < wpr ? mask0 + c * mask_pitch + 8u * s + 2u * q : kOutOfRange, 0, 0);
+        };
+        auto products = [&](uint32_t bits, const u32x4 (&w)[8]) {
+            const mf_i32x4 a = {(int32_t)expand_nibble(bits), (int32_t)expand_nibble(bits >> 4),
+                                (int32_t)expand_nibble(bits >> 8), (int32_t)expand_nibble(bits >> 12)};
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                acc[0][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, __builtin_bit_cast(mf_i32x4, w[t]), acc[0][t], 0, 0, 0);
+        };
+        u32x4 w0[8], w1[8];
+        uint32_t b0, b1;
+        load_packed(wave, w0, b0);
+        load_packed(wave + kActiveWaves, w1, b1);
+        for (int s = wave; s < wpr; s += 2 * kActiveWaves) {
+            products(b0, w0);
+            load_packed(s + 2 * kActiveWaves, w0, b0);
+            __builtin_amdgcn_sched_barrier(0);
+            products(b1, w1);
+            load_packed(s + 3 * kActiveWaves, w1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     // Register j of lane 16 q + c is row 4 q + j: the rows below 8 are in the
     // lower half of the lanes.  The eight waves' sums go through LDS (layout as
@@ -624,7 +677,15 @@ __device__ __attribute__((always_inline)) inline void active_tile(const int8_t* 
         return ((j * kActiveWaves + source) * 32 + lane) * 2 + (h ^ ((lane >> 2) & 1));
     };
     __syncthreads();  // the list has been read
-    if (l < 32) {
+    if (l < 32 && !listed) {  // channel 16 t + c
+        int32_t* words = reinterpret_cast<int32_t*>(part);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                words[4 * half_at(j, wave, 16 * q + 2 * t + c / 8, c / 4 % 2) + c % 4] = acc[0][t][j];
+    }
+    if (l < 32 && listed) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -646,13 +707,14 @@ __device__ __attribute__((always_inline)) inline void active_tile(const int8_t* 
 // Several projections of the same up to 8 rows in one launch, longest K first.
 struct ActiveItems {
     const int8_t* W[kMfmaMaxItems];
+    const int8_t* P[kMfmaMaxItems];   // packed copy
     const float* scale[kMfmaMaxItems];
     int64_t mask_off[kMfmaMaxItems];  // words
     int64_t out_off[kMfmaMaxItems];   // floats
     int32_t K[kMfmaMaxItems];
 };
 
-template <bool NT>
+template <bool NT, bool NTP>
 __global__ __launch_bounds__(kActiveBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_active_items(
     const ActiveItems items, int N, int n_coltiles, const uint64_t* __restrict__ mask, int B,
     float* __restrict__ out)
@@ -665,7 +727,8 @@ __global__ __launch_bounds__(kActiveBlock) __attribute__((amdgpu_waves_per_eu(4)
     const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint64_t*>(mask + items.mask_off[item]), 0, B * pitch, kBufferFlags);
     float* o = out + items.out_off[item];
-    active_tile<NT>(items.W[item], items.scale[item], K, N, n0, mres, 0, pitch, B, lds,
+    active_tile<NT, NTP>(items.W[item], items.P[item], items.scale[item], K, N, n0, mres, 0,
+                         pitch, B, lds,
                     [&](int r) -> float* { return r < B ? o + (int64_t)r * N : nullptr; });
 }
 

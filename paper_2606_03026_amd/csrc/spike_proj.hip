@@ -276,17 +276,23 @@ bool launch_stream_mat(const spike_stream* s, const uint64_t* masks, float* out,
 // rows (k_active_items) instead of all packed weights: up to 8 rows, and
 // enough weight bytes that what is not read pays for the column lists.
 // Measured, cold weights, spikes of a serving batch (a hot twentieth of the
-// columns, 0.10 elsewhere), active columns against all: 260 MB 17 us against 48
-// for 1 row, 31 against 49 for 4, 38 against 51 for 7; 118 MB 20 against 24 for
-// 8 rows, 108 MB 27 against 27; 65 MB 11 against 15 for 2 rows, 14.5 against 14.9
-// for 5, 15.8 against 15.1 for 8; 29 MB 7.7 against 8.8 for 1 row, 9.3 against 8.9
-// for 4.  Sparser rows gain more (0.03: 260 MB 22 us for 8 rows); at a rate of
-// 0.4, where four rows touch nearly every column, the lists cost 20 - 25%.
+// columns, 0.10 elsewhere), active columns against all: 260 MB 16 us against 49
+// for 1 row, 31 against 51 for 4, 42 against 52 for 8; 115 MB 19 against 25 for 4
+// rows, 25 against 25 for 7; 65 MB 11 against 18 for 2 rows, 13 against 18 for 4; 29
+// MB 6.6 against 8.8 for 1 row.  Sparser rows gain more (0.03: 260 MB 22 us for 8
+// rows).  Tiles whose rows touch most columns turn to the packed copy by
+// themselves; the count before that costs 1 to 2.5 us (at 0.4, 260 MB 54 us
+// against 51 for 4 rows, 115 MB 27 against 25, 65 MB 19.4 against 18.2).  A launch
+// of few tiles leaves compute units idle for longer than its lists save: 2 x 4096
+// -> 4096, 64 tiles, one row at 0.4 11.3 us against 8.5, 7.7 against 8.5 at 0.1 (22
+// pairs of 64 and 6144, 256 channels, 88 tiles, 9.0 against 12.6 at 0.1).
 constexpr int64_t kActiveMinBytes = 24ll << 20;
 constexpr int64_t kActiveRowBytes = 13ll << 20;
+constexpr int kActiveMinTiles = 80;
 // Weights that do not stay in the 256 MB Infinity Cache from one step to the
 // next are marked nontemporal where most of them are read: 260 MB and 7 rows 38
-// us against 42 without, 2 rows 22 against 21; 118 MB and 8 rows 23 against 20.
+// us against 42 without, 2 rows 22 against 21; 118 MB and 8 rows 23 against 20;
+// packed tiles, 260 MB, 54 us against 57.
 constexpr int64_t kActiveNtBytes = 200ll << 20;
 
 bool launch_active_items(const spike_proj_t* projs, int32_t n_proj, const spk::MfmaItems& mi, const uint64_t* masks,
@@ -310,18 +316,21 @@ bool launch_active_items(const spike_proj_t* projs, int32_t n_proj, const spk::M
             order[at] = order[at - 1];
         order[at] = j;
     }
-    if (bytes < std::max(kActiveMinBytes, B * kActiveRowBytes))
+    const int col_tiles = (N + spk::kColChannels - 1) / spk::kColChannels;
+    if (bytes < std::max(kActiveMinBytes, B * kActiveRowBytes) || (int64_t)n_proj * col_tiles < kActiveMinTiles)
         return false;
     for (int i = 0; i < n_proj; ++i) {
         const int j = order[i];
         items.W[i] = projs[j]->W;
+        items.P[i] = projs[j]->packed;
         items.scale[i] = mi.scale[j];
         items.mask_off[i] = mi.mask_off[j];
         items.out_off[i] = mi.out_off[j];
         items.K[i] = projs[j]->K;
     }
-    const int col_tiles = (N + spk::kColChannels - 1) / spk::kColChannels;
-    const auto fn = B > 4 && bytes > kActiveNtBytes ? spk::k_active_items<true> : spk::k_active_items<false>;
+    const auto fn = bytes <= kActiveNtBytes ? spk::k_active_items<false, false>
+                    : B > 4                 ? spk::k_active_items<true, true>
+                                            : spk::k_active_items<false, true>;
     hipLaunchKernelGGL(fn, dim3((unsigned)(n_proj * col_tiles)), dim3(spk::kActiveBlock), spk::active_lds(items.K[0]),
                        st, items, N, col_tiles, masks, B, out);
     *err = hipGetLastError();
@@ -609,6 +618,7 @@ int static_scratch(int dev, hipStream_t st, uint32_t** out)
 }
 
 constexpr int kFusedMinTiles = 256;  // compute units
+constexpr int kFusedSteps = 6;       // k-steps of a wave
 
 // The projections of spike_stack_forward_fused in one launch (arguments
 // checked); SPIKE_EUNSUPPORTED where they cannot run together.
@@ -627,11 +637,12 @@ int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* mas
     }
     if (int rc = check_device(projs[0]->device))
         return rc;
-    // One ring plan for all items, with waves for the longest K: a wave past a
-    // short projection's last k-step adds zeros.  (A plan cut to the shortest K
-    // ran K = 16384 beside K = 64, 512 channels, in single waves: one row 28.0 us
-    // against 8.7 for the two launches, now 7.3; 6144 beside 64, 1536 channels, 32
-    // rows 41 against 9.7, now 6.1.)
+    // One ring plan for all items.  Its waves may outnumber the k-steps of the
+    // shortest K, whose idle waves add zeros, while the longest has more than
+    // kFusedSteps per wave.  (A plan cut to the shortest K ran  K = 16384 beside K = 64, 512
+    // channels, in single waves: one row 28.0 us against 8.7 for the two launches,
+    // now 7.3; 6144 beside 64, 1536 channels, 32 rows 41 against 9.7, now 6.1.  22
+    // pairs of 512 and 2048, 512 channels, take 9.1 us with 8 waves, 9.7 with 16.)
     // Tiles of up to 64 rows by 48 channels, two k-steps in flight per wave;
     // 8 waves for 64-row tiles (measured on the 64-row decode stack, 1408
     // workgroups over 44 projections: 49 us per step against 57 us with 16
@@ -665,10 +676,14 @@ int forward_fused(const spike_proj_t* projs, int32_t n_proj, const uint64_t* mas
     while (h0->mfma_col_sets == 0 && p.cs > 1 && too_few())
         p.cs = 1;
     const spk::MfmaPlan want = p;
-    bool found = N % spk::kMfmaNAlign == 0 && spk::mfma_ring_plan(p, max_wpr, N);
+    const int min_wpr = (int)words_per_row(min_K);
+    int kw = 1;
+    while (kw * kFusedSteps < max_wpr)
+        kw *= 2;
+    bool found = N % spk::kMfmaNAlign == 0 && spk::mfma_ring_plan(p, std::max(min_wpr, kw), N);
     if (found && spk::mfma_lds_bytes(p.rt, p.cs, max_wpr) > spk::kMfmaMaxLds) {
         p = want;  // fewer waves may come with narrower tiles
-        found = spk::mfma_ring_plan(p, (int)words_per_row(min_K), N);
+        found = spk::mfma_ring_plan(p, min_wpr, N);
     }
     if (!found)
         return fail(SPIKE_EUNSUPPORTED, "no matrix-core plan serves N = %d, K >= %d, B = %d in one launch", N, min_K, B);

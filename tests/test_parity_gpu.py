@@ -370,8 +370,8 @@ def test_stack_forward_routes(sp, B, variant):
 @pytest.mark.parametrize("B,N,Ks,kernel", [
     (1, 512, (64, 16384), "k_mfma_items<1,1,16,2>"), (8, 512, (16384, 1, 65), "k_mfma_items<1,1,16,2>"),
     (32, 1536, (64, 6144), "k_mfma_items<1,1,16,2>"), (33, 1536, (6144, 64, 700, 1), "k_mfma_items<2,3,16,2>"),
-    (64, 1536, (64, 6144) * 6, "k_mfma_items<4,3,8,2>"), (64, 512, (1, 1000) * 20, "k_mfma_items<4,2,8,4>"),
-    (17, 80, (33, 129, 1025), "k_mfma_items<1,1,16,2>"), (64, 8192, (64, 7616), "k_mfma_items<4,1,1,2>")])
+    (64, 1536, (64, 6144) * 6, "k_mfma_items<4,3,8,2>"), (64, 512, (1, 1000) * 20, "k_mfma_items<4,1,2,2>"),
+    (17, 80, (33, 129, 1025), "k_mfma_items<1,1,4,4>"), (64, 8192, (64, 7616), "k_mfma_items<4,1,1,2>")])
 def test_stack_of_unlike_k(sp, B, N, Ks, kernel):
     rng = np.random.default_rng([42, 36, B, N, len(Ks)])
     host = [(rng.integers(-127, 128, (K, N)).astype(np.int8), rng.uniform(1e-3, 1e-2, N).astype(np.float32)) for K in Ks]
@@ -846,6 +846,45 @@ def test_fused_active_columns(sp, B, N, repeat, w_offset):
         if K % 64:
             m[:, -1] &= np.uint64((1 << (K % 64)) - 1)
         np.testing.assert_array_equal(bits32(got[i]), bits32(oracle.spike_forward(W, sc, m, threads=8)), err_msg=f"item {i}")
+
+
+# Where the fused launch over the active columns lists them and where it reads
+# the packed copy: unions of the longest list and one more, none and all, in
+# one launch; K of one and of two passes of columns, a ragged last channel tile, junk
+# past K; every kernel variant, and the routes around the rule's bytes and tiles.
+@pytest.mark.parametrize("B,K,N,n,kernel", [
+    (1, 1001, 1552, 20, "k_active_items<0,0>"), (7, 1001, 1552, 64, "k_active_items<0,0>"), (2, 16384, 272, 64, "k_active_items<0,1>"),
+    (5, 16384, 272, 64, "k_active_items<1,1>"), (8, 8193, 528, 64, "k_active_items<1,1>"), (4, 8193, 528, 64, "k_active_items<0,1>"),
+    (1, 16384, 272, 26, "k_mfma_items<1,1,16,2>"), (1, 16384, 272, 27, "k_active_items<0,0>"), (8, 1001, 1552, 64, "k_mfma_items<1,1,16,2>"),
+    (1, 1001, 1552, 15, "k_mfma_items<1,1,16,2>")])
+def test_fused_active_columns_or_packed_copy(sp, B, K, N, n, kernel):
+    rng = np.random.default_rng([42, 37, B, K, N])
+    W = rng.integers(-128, 128, (K, N)).astype(np.int8)
+    scale = rng.uniform(-1e-2, 1e-2, N).astype(np.float32)
+    h = sp.spike_proj_create_reserved(dev(W), dev(scale), B)
+    most = K * 25 // 32 if kernel in ("k_active_items<0,1>", "k_active_items<1,1>") else K * 5 // 8
+    masks, clean = [], []
+    for i in range(n):
+        union = (most, most + 1, 0, K, most - 1, 100)[i % 6]
+        cols = rng.choice(K, union, replace=False)
+        bits = np.zeros((B, K), bool)
+        bits[:, cols] = rng.random((B, union)) < 0.3
+        bits[rng.integers(0, B, union), cols] = True
+        m = wl.pack_bits(bits)
+        clean.append(m.copy())
+        if K % 64:
+            m[:, -1] |= np.uint64((~((1 << (K % 64)) - 1)) & 0xFFFFFFFFFFFFFFFF)
+        masks.append(m)
+    dm = dmask(np.concatenate([m.ravel() for m in masks]))
+    flat = torch.full((n * B * N + 8,), 3.5, device="cuda")
+    out = flat[:n * B * N]
+    assert kernels(lambda s: sp.spike_stack_forward_fused([h] * n, dm, B, out, stream=s)) == [kernel]
+    sp.spike_stack_forward_fused([h] * n, dm, B, out)
+    torch.cuda.synchronize()
+    assert (flat[n * B * N:] == 3.5).all()
+    got = out.cpu().numpy().reshape(n, B, N)
+    for i in list(range(6)) + [n - 1]:
+        np.testing.assert_array_equal(bits32(got[i]), bits32(oracle.spike_forward(W, scale, clean[i], threads=8)), err_msg=f"item {i}")
 
 
 @pytest.mark.parametrize("B", [1, 17, 64, 65, 130])
