@@ -221,9 +221,10 @@ int spike_mfma_plans(int32_t *codes, int32_t cap);
  * projection with default tuning and enough reserved rows (assuming the
  * matrix-core copy of W could be allocated): *path receives
  * SPIKE_PATH_GATHER or SPIKE_PATH_MFMA, *plan the matrix-core plan code (as
- * in spike_mfma_plans) or 0 (batches of 144 and more tiles of 128 rows x 128
- * channels run in a wide form instead of the reported plan, unless a plan
- * control is set).  Host-only: no device is touched. */
+ * in spike_mfma_plans) or 0.  Unless a plan control is set, batches of enough
+ * tiles of 128 rows x 128 channels run in a wide form instead of the reported
+ * plan: at least 144 tiles, 288 from 257 on, for 64 < K <= 8640 (from 257 on at
+ * least 336 for K <= 192).  Host-only: no device is touched. */
 int spike_proj_plan_query(int32_t K, int32_t N, int32_t B, int32_t *path, int32_t *plan);
 
 /* Active-index extraction (Sec. 2.2, A = {k : x_k = 1}) as a standalone

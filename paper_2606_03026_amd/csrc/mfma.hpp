@@ -991,21 +991,29 @@ inline hipError_t launch_mfma(const MfmaPlan& p, const int8_t* P, const float* s
 
 // Whether B rows run in the wide form: one tile takes a compute unit about as
 // long as the other form takes for 110 - 150 of its tiles over the whole chip, so
-// each round of 256 tiles has to be full enough.  Measured, wide against 64-row
-// tiles: 6144 -> 1536, 96 tiles 26.0 us against 19.5, 144 tiles 26.6 against 28.0,
-// 240 tiles 29.2 against 43.1; 1536 -> 1536, 96 tiles 11.4 against 11.8; 4096 ->
-// 4096, 128 tiles 20.1 against 25.6; 512 -> 4096, 192 tiles 9.4 against 12.8; 2048
-// -> 256, 40 tiles 12.3 against 10.4.
-constexpr int kWideMinTiles = 144;
+// each round of 256 tiles has to be full enough: 144 tiles on average.  That is
+// where 6144 inputs break even.  Measured, wide against 64-row tiles: 6144 -> 1536,
+// 96 tiles 26.0 us against 19.5, 144 tiles 25.0 against 26.0, 156 tiles 25.1
+// against 32.2, 240 tiles 28.8 against 42.0, 252 tiles 30.0 against 47.9, 288 tiles
+// 50.8 against 49.2; -> 4096, 320 tiles 51 against 68, 640 tiles 78 against 132;
+// 2048 -> 256, 40 tiles 12.3 against 10.4; 512 -> 4096, 160 tiles 9.9 against 12.5.
+// Shorter K break even earlier (1536 -> 1536, 96 tiles 11.4 against 11.8; 4096 ->
+// 4096, 128 tiles 20.1 against 25.6), which the rule leaves to the 64-row tiles, as
+// it does batches of 257 .. 287 tiles, whose second round would be nearly empty.
+// One k-step does not pay for the wider sums (64 inputs, 160 tiles 9.2 against
+// 8.0, 320 tiles 15.1 against 11.0), two or three not for a second round of fewer
+// than 80 (128 inputs, 288 tiles 15.2 against 14.2, 640 tiles 22.3 against 24.3).
+constexpr int kWideMinTiles = 144, kWideMinTilesShortK = 168;
 inline bool mfma_wide_applies(int K, int N, int B)
 {
     const int wpr = (K + 63) / 64;
     const int64_t row_tiles = (B + kWideRows - 1) / kWideRows;
     const int64_t tiles = row_tiles * ((N + kWideChannels - 1) / kWideChannels);
-    if (wide_lds_bytes(wpr) > kWideMaxLds || row_tiles * kWideRows * wpr * (int64_t)sizeof(uint64_t) >= (1ll << 31) ||
-        tiles > 0x7ffffff)
+    if (wpr < 2 || wide_lds_bytes(wpr) > kWideMaxLds ||
+        row_tiles * kWideRows * wpr * (int64_t)sizeof(uint64_t) >= (1ll << 31) || tiles > 0x7ffffff)
         return false;
-    return tiles >= kWideMinTiles * ((tiles + 255) / 256);
+    const int64_t rounds = (tiles + 255) / 256;
+    return tiles >= rounds * (rounds > 1 && wpr < 4 ? kWideMinTilesShortK : kWideMinTiles);
 }
 
 inline hipError_t launch_mfma_wide(const int8_t* P, const float* scale, int K, int N, const uint64_t* mask, int B,

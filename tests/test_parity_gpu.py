@@ -1016,6 +1016,31 @@ def test_matrix_core_wide_form(sp, K, N, B, p, offset):
     np.testing.assert_array_equal(got_acc[offset:-8].reshape(B, N)[some], oracle.spike_acc(prob["W"], prob["masks"][some]))
 
 
+@pytest.mark.parametrize("K,N,B,wide", [
+    (64, 1536, 1537, False), (65, 1536, 1409, True), (65, 1536, 1408, False), (192, 256, 18432, False), (192, 256, 21504, True),
+    (193, 256, 18432, True), (193, 256, 18304, False), (193, 256, 32768, True), (6144, 1536, 2688, True), (6144, 1536, 2689, False),
+    (8640, 1536, 1409, True), (8641, 1536, 1409, False)])
+def test_matrix_core_wide_form_route(sp, K, N, B, wide):
+    """The batches that the wide form takes, on either side of every line of its
+    rule; a set plan control keeps the tiled form."""
+    W = torch.zeros((K, N), dtype=torch.int8, device="cuda")
+    h = sp.spike_proj_create_reserved(W, torch.ones(N, device="cuda"), B)
+    mask = torch.zeros((B, wl.words_per_row(K)), dtype=torch.int64, device="cuda")
+    out = torch.zeros((B, N), device="cuda")
+    route = lambda: kernels(lambda s: sp.spike_proj_forward(h, mask, B, out, stream=s))[0].split("<")[0]  # noqa: E731
+    assert route() == ("k_mfma_wide" if wide else "k_mfma")
+    sp.spike_proj_tune(h, sp.SPIKE_TUNE_MFMA_ROW_TILE, 4 if K < 8000 else 2)
+    assert route() == "k_mfma"
+    h.close()
+
+
+def test_matrix_core_wide_form_two_words(sp):
+    """Two k-steps for the four waves along K: the third and fourth have none."""
+    p = wl.small_problem(65, 2064, 1152, 0.5, seed=3)
+    h = sp.spike_proj_create_reserved(dev(p["W"]), dev(p["scale"]), 1152)
+    assert_parity(sp, h, p["W"], p["scale"], p["masks"])
+
+
 def test_matrix_core_rejects_unaligned_N(sp):
     p = wl.small_problem(128, 100, 4, 0.3)
     h, *_ = make(sp, p["W"], p["scale"])
