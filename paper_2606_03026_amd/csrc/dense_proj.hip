@@ -194,9 +194,13 @@ DensePlan make_plan(int32_t K, int32_t M, int32_t B, int q_align)
         // evenly over the batch tiles, a multiple of 8 each so that the
         // workgroups of one row step sit on one XCD and share its L2
         const int64_t resident = kCUs * (p.nb == 1 && npl <= 3 ? 2 : 1);
-        int64_t rw = std::min<int64_t>(steps, std::max<int64_t>(1, resident / b_tiles));
-        if (rw >= 8)
-            rw = rw / 8 * 8;
+        // (rounded down only where each walks several steps anyway: 12,000 rows are 375
+        // steps, and 368 workgroups took 10.3 us, 7 of them two steps, 376 take 8.3)
+        int64_t rw = std::max<int64_t>(1, resident / b_tiles);
+        if (steps > rw)
+            rw = rw >= 8 ? rw / 8 * 8 : rw;
+        else
+            rw = (steps + 7) / 8 * 8 <= rw ? (steps + 7) / 8 * 8 : steps;
         p.row_wgs = (int)rw;
         p.bc = (int)std::min<int64_t>(b_tiles * 16 * p.nb, 1 << 30);
         p.wgs = b_tiles * rw;

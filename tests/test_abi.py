@@ -111,6 +111,20 @@ def test_automatic_matrix_core_plans_are_instantiated(sp):
     assert sp.spike_proj_plan_query(1536, 1000, 1)[0] == sp.SPIKE_PATH_GATHER
 
 
+def test_dense_batches_give_no_workgroup_a_second_step_for_rounding(sp):
+    """Row steps that fit the workgroups of one round get one each: their count is
+    rounded up to a multiple of 8 where that fits too, never down."""
+    for K, resident in ((528, 512), (1536, 512), (2048, 256), (4096, 256)):
+        for M in (1031, 2050, 4000, 6144, 8191, 12000):
+            for B in (9, 16):
+                wgs = sp.dense_proj_plan(K, M, B)["workgroups"]
+                tile = 16 if (M + 31) // 32 < 256 or K > 3584 else 32
+                steps = -(-M // tile)
+                assert wgs <= resident, (K, M, B, wgs)
+                if steps <= resident:
+                    assert wgs >= steps, (K, M, B, wgs, steps)
+
+
 def test_dense_argument_validation_before_any_hip_call(sp):
     lib = sp.raw_library()
     d = 0x1000  # never dereferenced: validation fails first
