@@ -64,8 +64,9 @@ int dense_proj_forward(const int8_t *Q, const float *scale, int32_t K, int32_t M
 /* Kernels: DENSE_KERNEL_REGISTER keeps each lane's slice of the activations
  * in registers (16-byte aligned Q, K % 16 == 0, K <= 4096): a vector form of
  * up to 4 batch rows per launch and, for batches of more than 8 rows, or of
- * more than 2 where M >= 1024, a matrix-core form that takes all rows in one
- * launch with the same FMAs in the same order (identical bits).
+ * more than 2 where M >= 1024 (more than 4 for some large M with K <= 1280), a
+ * matrix-core form that takes all rows in one launch with the same FMAs in the
+ * same order (identical bits).
  * DENSE_KERNEL_STAGED stages the activations in LDS (any K, alignment, up to
  * 8 rows per launch).  The choice depends on K and Q's alignment only. */
 #define DENSE_KERNEL_STAGED 1

@@ -162,6 +162,24 @@ struct DensePlan {
 
 constexpr int kCUs = 256;
 
+// Batches of 3 and 4 rows of a large Q that one or two vector launches serve
+// faster than a matrix-core one.  The matrix-core form works on all of the last
+// 512 columns of a row, the vector form reads the ones that are there.  Measured,
+// 3 rows, vector against matrix-core: K = 512 (one launch, whose 8,192 lane groups
+// take their rows four at a time) 20,000 rows 7.5 us against 7.1, 30,000 7.7 against
+// 8.5, 40,000 11.1 against 9.8, 57,344 11.3 against 12.6, 100,000 16 against 21; K =
+// 768 57,344 rows 21.3 against 20.6, 100,000 31 against 37, K = 1024 39 against 35; K
+// = 1040 32,000 rows 17.7 against 18.5, 57,344 26 against 30, K = 1360 29.5 against
+// 30.8 (4 rows 31.2 against 30.9).
+bool vector_rows(int32_t K, int32_t M, int32_t B, int npl)
+{
+    if (B > 4)
+        return false;
+    const int64_t rounds = (M + 4 * 8192 - 1) / (4 * 8192);
+    return (npl == 1 && M > 22700 * rounds) || (npl == 2 && K <= 768 && M >= 65536) ||
+           (npl == 3 && K <= 1280 && M >= 49152);
+}
+
 // q_align: the largest power of two (up to 16) dividing Q's address.  The
 // kernel and load width depend on K and q_align only, never on B, so a row's
 // summation order is the same in every batch.
@@ -182,7 +200,7 @@ DensePlan make_plan(int32_t K, int32_t M, int32_t B, int q_align)
     // 9.9), and below 1024 rows of Q the matrix-core form has too few row
     // steps to be worth it before 8 rows (1536 -> 300: 9 rows 20.6 against
     // 8.3).  (A set DENSE_TUNE_WG_PER_CU asks for the vector form's grid.)
-    if (p.kernel == DENSE_KERNEL_REGISTER && wpc == 0 && (B > 8 || (B > 2 && M >= 1024))) {
+    if (p.kernel == DENSE_KERNEL_REGISTER && wpc == 0 && (B > 8 || (B > 2 && M >= 1024 && !vector_rows(K, M, B, npl)))) {
         p.npl = npl;
         p.nb = B > 16 ? mat_max_nb(npl) : 1;
         const int64_t b_tiles = (B + 16 * p.nb - 1) / (16 * p.nb);

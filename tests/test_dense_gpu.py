@@ -22,6 +22,7 @@ import torch
 
 import oracle
 from paper_2606_03026_amd import workloads as wl
+from tests.launches import kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -258,6 +259,26 @@ def test_dense_register_kernel_grid_does_not_change_results(sp, forced_kernel):
     np.testing.assert_array_equal(bits32(outs[0]), bits32(outs[1]))
     np.testing.assert_array_equal(bits32(outs[0]), bits32(outs[2]))
     assert_within_bound(outs[0], p["Q"], p["scale"], p["x"])
+
+
+@pytest.mark.parametrize("K,M,B,matrix", [
+    (512, 1024, 3, True), (512, 1023, 3, False), (512, 1024, 2, False), (512, 1023, 9, True), (1536, 57344, 3, True),
+    (512, 22700, 3, True), (512, 22701, 3, False), (512, 32768, 4, False), (512, 32769, 4, True), (512, 45400, 4, True),
+    (512, 45401, 4, False), (512, 45401, 5, True), (16, 200000, 4, False), (768, 65535, 3, True), (768, 65536, 3, False),
+    (784, 65536, 3, True), (1280, 49152, 4, False), (1280, 49151, 4, True), (1296, 49152, 4, True), (1280, 49152, 5, True)])
+def test_dense_vector_or_matrix_core_form(sp, K, M, B, matrix):
+    """Which form of the register kernel a batch takes, on either side of every
+    line of the rule, and the same bits from both."""
+    Q = torch.randint(-127, 128, (M, K), dtype=torch.int8, device="cuda")
+    scale, x = torch.rand(M, device="cuda") * 1e-2, torch.randn((B, K), device="cuda")
+    y, ref = torch.empty((B, M), device="cuda"), torch.empty((B, M), device="cuda")
+    names = kernels(lambda s: sp.dense_proj_forward(Q, scale, x, B, y, stream=s))
+    assert {n.split("<")[0] for n in names} == {"k_dense_mat" if matrix else "k_dense_reg"}
+    sp.dense_proj_forward(Q, scale, x, B, y)
+    for b in range(B):  # one row at a time: the vector form
+        sp.dense_proj_forward(Q, scale, x[b:b + 1], 1, ref[b:b + 1])
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int32), ref.view(torch.int32))
 
 
 # K for the chunk counts per lane of every matrix-core instantiation, with
