@@ -261,6 +261,32 @@ def test_dense_register_kernel_grid_does_not_change_results(sp, forced_kernel):
     assert_within_bound(outs[0], p["Q"], p["scale"], p["x"])
 
 
+# K for the chunk counts per lane of every matrix-core instantiation, with
+# ragged tails; M around the 16- and 32-row steps, past one step per workgroup,
+# and where 3 to 16 rows take two weight tiles a step; B around the 16- and 32-row
+# batch tiles.
+MATRIX_CORE_K = [16, 80, 512, 528, 1024, 1536, 2048, 2560, 3072, 3584, 4096]
+MATRIX_CORE_MB = [(1, 9), (31, 16), (33, 17), (1031, 3), (2050, 33), (9001, 50), (8161, 5), (9001, 9), (16001, 16)]
+
+
+def test_dense_matrix_core_grid_reaches_every_instantiation(sp):
+    """The grid below launches every k_dense_mat<chunks, batch tiles, weight
+    tiles> that the plan can choose: two batch tiles up to 4 chunks, two weight
+    tiles where activations, accumulators and weights fit 200 registers, one
+    where a launch has few steps."""
+    want = set()
+    for npl in range(1, 9):
+        for nb in (1, 2) if npl <= 4 else (1,):
+            want |= {f"k_dense_mat<{npl},{nb},{rt}>" for rt in ((1, 2) if 16 * npl * nb + 32 * nb + 8 * npl <= 200 else (1,))}
+    got = set()
+    for K in MATRIX_CORE_K:
+        for M, B in MATRIX_CORE_MB:
+            Q, scale = torch.zeros((M, K), dtype=torch.int8, device="cuda"), torch.zeros(M, device="cuda")
+            x, y = torch.zeros((B, K), device="cuda"), torch.zeros((B, M), device="cuda")
+            got |= set(kernels(lambda s: sp.dense_proj_forward(Q, scale, x, B, y, stream=s)))
+    assert got == want
+
+
 @pytest.mark.parametrize("K,M,B,matrix", [
     (512, 1024, 3, True), (512, 1023, 3, False), (512, 1024, 2, False), (512, 1023, 9, True), (1536, 57344, 3, True),
     (512, 22700, 3, True), (512, 22701, 3, False), (512, 32768, 4, False), (512, 32769, 4, True), (512, 45400, 4, True),
@@ -281,11 +307,8 @@ def test_dense_vector_or_matrix_core_form(sp, K, M, B, matrix):
     assert torch.equal(y.view(torch.int32), ref.view(torch.int32))
 
 
-# K for the chunk counts per lane of every matrix-core instantiation, with
-# ragged tails; M around the 16- and 32-row steps and past one step per
-# workgroup; B around the 16- and 32-row batch tiles.
-@pytest.mark.parametrize("K", [16, 80, 512, 528, 1024, 1536, 2048, 2560, 3072, 3584, 4096])
-@pytest.mark.parametrize("M,B", [(1, 9), (31, 16), (33, 17), (1031, 3), (2050, 33), (9001, 50)])
+@pytest.mark.parametrize("K", MATRIX_CORE_K)
+@pytest.mark.parametrize("M,B", MATRIX_CORE_MB)
 def test_dense_matrix_core_batches_match_vector_form(sp, forced_kernel, K, M, B):
     """The matrix-core form of the register kernel (batches) runs the same
     FMAs in the same order as the vector form (forced by a grid cap): equal
