@@ -72,9 +72,12 @@ int spike_quantize_int8(const float* W, int32_t M, int32_t K, int32_t layout, in
     // workgroups read it, and one CU takes in about 36 GB/s.  Short rows pay from
     // 1024 rows on (1536 x 1536: 8.4 us against 11.2), longer ones only where
     // about half the CUs have a workgroup (2048 x 4096: 14.1 against 15.7; 1536 x 6144:
-    // 17.4 against 16.9; 400 x 6000: 14.5 against 11.1).
+    // 17.4 against 16.9; 400 x 6000: 14.5 against 11.1).  Rows of less than 96 values
+    // leave most of a wave's lanes idle, which counts once there are many of them
+    // (64 values: 16,384 rows 6.4 us against 8.6, 65,536 17.6 against 17.1, 262,144 68.7
+    // against 62.3; 96 values, 262,144 rows 69 against 71).
     if (layout == SPIKE_LAYOUT_COL_MAJOR && K % 4 == 0 && M % spk::kColRows == 0 && aligned(W, 16) &&
-        aligned(Q, 16) && ((K <= 2048 && M >= 1024) || (K <= spk::kQuantRowsMaxK && M >= 2048))) {
+        aligned(Q, 16) && ((K <= 2048 && M >= 1024 && (K >= 96 || M < 65536)) || (K > 2048 && K <= spk::kQuantRowsMaxK && M >= 2048))) {
         const int nv = (K + 255) / 256;
         const int groups = M / spk::kColRows;
         const dim3 grid((groups + 7) / 8 * 8);

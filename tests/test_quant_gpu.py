@@ -11,6 +11,7 @@ import torch
 
 import oracle
 from paper_2606_03026_amd import workloads as wl
+from tests.launches import kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -182,6 +183,17 @@ def test_quantizer_rejects_bad_arguments(sp):
                                                    (48, 2048, 0, 0), (5, 8200, 0, 0)])
 def test_quantizer_column_major_paths(sp, M, K, w_offset, q_offset):
     assert_same(sp, weights(M, K, 6), sp.SPIKE_LAYOUT_COL_MAJOR, w_offset=w_offset, q_offset=q_offset)
+
+
+@pytest.mark.parametrize("M,K,one_pass", [
+    (1024, 2048, True), (1008, 2048, False), (2048, 2052, True), (2032, 2052, False), (2048, 4096, True), (2048, 4100, False),
+    (65536, 92, False), (65520, 92, True), (65536, 96, True), (1024, 4, True), (1030, 64, False), (1024, 62, False)])
+def test_quantizer_column_major_route(sp, M, K, one_pass):
+    """The sizes that take the one-pass export, on either side of every line of its rule."""
+    W, Q = torch.zeros((M, K), device="cuda"), torch.zeros((K, M), dtype=torch.int8, device="cuda")
+    scale = torch.zeros(M, device="cuda")
+    names = kernels(lambda s: sp.spike_quantize_int8(W, sp.SPIKE_LAYOUT_COL_MAJOR, Q, scale, stream=s))
+    assert [n.split("<")[0] == "k_quant_cols" for n in names] == ([True] if one_pass else [False, False])
 
 
 @pytest.mark.parametrize("layout", LAYOUTS)
