@@ -65,6 +65,7 @@
 #include <algorithm>
 
 #include "buffer.hpp"
+#include "bytes.hpp"
 #include "gather.hpp"
 #include "mfma.hpp"  // mf_i32x4
 
@@ -75,17 +76,6 @@ constexpr int kColBlock = 64 * kColWaves;
 constexpr int kColChannels = 128;  // channels of a workgroup
 constexpr int kColStep = 128;      // columns of a double step (two mask words)
 constexpr int kColumnMaxWords = 66 * 1024;  // spike words of a tile: two workgroups on a compute unit
-
-// Rows of four channels' bytes -> per channel the four rows' bytes.
-__device__ inline void transpose_bytes(const uint32_t (&r)[4], uint32_t (&ch)[4])
-{
-    const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
-    const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
-    ch[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
-    ch[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-    ch[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-    ch[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-}
 
 // The stream's projections for the matrix cores, longest K first: items are
 // (weight set, projection) pairs, item i = set i % n_sets of projection proj[i / n_sets].

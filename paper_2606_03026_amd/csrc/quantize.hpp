@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bytes.hpp"
+
 namespace spk {
 
 constexpr int kQuantBlock = 256;
@@ -194,17 +196,6 @@ __global__ __launch_bounds__(kQuantBlock) void k_quant_rows(const float* __restr
     }
 }
 
-// Byte i of d[j] becomes byte j of t[i].
-__device__ inline void transpose_4x4(const uint32_t (&d)[4], uint32_t (&t)[4])
-{
-    const uint32_t p0 = __builtin_amdgcn_perm(d[1], d[0], 0x05010400u), p1 = __builtin_amdgcn_perm(d[1], d[0], 0x07030602u);
-    const uint32_t q0 = __builtin_amdgcn_perm(d[3], d[2], 0x05010400u), q1 = __builtin_amdgcn_perm(d[3], d[2], 0x07030602u);
-    t[0] = __builtin_amdgcn_perm(q0, p0, 0x05040100u);
-    t[1] = __builtin_amdgcn_perm(q0, p0, 0x07060302u);
-    t[2] = __builtin_amdgcn_perm(q1, p1, 0x05040100u);
-    t[3] = __builtin_amdgcn_perm(q1, p1, 0x07060302u);
-}
-
 // Column-major export in one pass: a workgroup of 16 waves takes 16
 // consecutive rows, one per wave and held in its registers (lane l: float4
 // chunks l + 64 j, j < NV, so K <= 256 NV), reduces each row's maximum, writes
@@ -265,7 +256,7 @@ __global__ __launch_bounds__(64 * kColRows) void k_quant_cols(const float* __res
 #pragma unroll
             for (int a = 0; a < 4; ++a)
                 d[a] = codes[(4 * i + a) * n4 + c];
-            transpose_4x4(d, t);
+            transpose_bytes(d, t);
 #pragma unroll
             for (int a = 0; a < 4; ++a)
                 out[a][i] = t[a];
