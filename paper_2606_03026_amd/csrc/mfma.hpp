@@ -289,8 +289,10 @@ __device__ __attribute__((always_inline)) inline void mfma_tile(const int8_t* __
     // Spikes 16q .. 16q + 15 of row 16 ms + c at the wave's step i (one
     // 16-bit LDS read per row subtile), and the A-operands built from them.
     const uint16_t* xs16 = reinterpret_cast<const uint16_t*>(xs);
+    // (a wave without steps reads the last word for its step 0 and multiplies nothing)
+    const int first_word = min(wave, wpr - 1);
     auto read_bits = [&](int i, uint32_t (&b)[RT]) {
-        const int s = min(wave + i * KW, wpr - 1);  // a wave without steps reads, and multiplies, nothing of its own
+        const int s = first_word + i * KW;
 #pragma unroll
         for (int ms = 0; ms < RT; ++ms)
             b[ms] = xs16[((16 * ms + c) * pitch + s) * 4 + q];
