@@ -6,8 +6,8 @@
 // batch: acc[t][n] = sum_k x[t][k] Q[n][k] with x in {0,1}.  The gather reads
 // every active column once per token; here a tile of up to 64 tokens reads the
 // columns that any of them activates once.  (64 while every K of the stream is at
-// most 8192, 32 up to 16256, 16 beyond: kColumnMaxWords.)  Products are 0 or a weight and INT32 sums are exact, so
-// the results have the gather's bits.
+// most 8192, 32 up to 16256, 16 beyond: kColumnMaxWords.)  Products are 0 or a
+// weight and INT32 sums are exact, so the results have the gather's bits.
 //
 // Operands.  A step is 64 of the 128 columns of a double step; lane
 // 16 q + c holds, of 8 consecutive channels 8 c .. 8 c + 7 of the wave's 128,
@@ -49,12 +49,13 @@
 // they share).  The token tiles of one weight tile run side by side on one XCD.
 //
 // Where most columns are active it is bound by HBM: 250 tokens over 4 copies of
-// 44 projections (1.04 GB of weights, 68 MB of results) take 206 us, 5.4 TB/s
+// 44 projections (1.04 GB of weights, 68 MB of results) take 204 us, 5.4 TB/s
 // (the gather 1346 us); 30 us of that are the stores (switched off in a timing
 // copy), and a plain nontemporal read of 1 GiB takes 155 us.  Spike dwords read
 // from global memory with each double step instead of staged in LDS, and sums
-// stored 16 bytes of every 32 at a time, took 241 us; the matrix and vector
-// units are busy about 26 and 20 us of it.  Where few are, it is bound by the
+// stored 16 bytes of every 32 at a time, took 241 us.  By its counters the matrix
+// units are busy for 26 us and the vector ALUs for 49, and its waves wait for
+// memory 60% of their time.  Where few columns are active, it is bound by the
 // phases of a workgroup (spike words, count, list, first weights, sums), about
 // 12,000 cycles before and after the weights.
 #pragma once
@@ -482,8 +483,9 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(RT ==
 // others' weights are not read.
 //
 // The union of the rows' spikes is counted; up to 5/8 of the columns (25/32 where
-// the packed copy comes from HBM at every step) it becomes a list in LDS with a byte per column holding which rows are active there (8 x
-// 8 bit transposes of the rows' bytes).  A step is 64 entries of the list, lane
+// the packed copy comes from HBM at every step) it becomes a list in LDS with a
+// byte per column holding which rows are active there (8 x 8 bit transposes of the
+// rows' bytes).  A step is 64 entries of the list, lane
 // 16 q + c taking entries 16 q .. 16 q + 15: its weight loads go to those
 // columns, and the spike operand of row c is bit c of the entries' row bytes, a
 // shift and an AND per four columns.  Entries past the list name column K, whose
@@ -492,7 +494,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(RT ==
 // columns.  Sums and stores are as above, but with 8 waves to a workgroup.
 //
 // What bounds the list is the random 128-byte reads: 7 rows of the 44-projection
-// stack, 143 MB of active columns, take 37 us, of which 8 are the launch, the
+// stack, 143 MB of active columns, take 38 us, of which 8 are the launch, the
 // lists and the sums (a timing copy with one step per wave); 4 waves a
 // workgroup take 40, and wider tiles (2 or 3 x 128 channels sharing a list)
 // 44 and 50: half as many workgroups leave compute units idle.  Where the lines

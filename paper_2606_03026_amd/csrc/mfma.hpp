@@ -500,8 +500,10 @@ __global__ __launch_bounds__(64 * KW) void k_mfma_items(const MfmaItems items, i
 // spike words and the sum over the four k-waves (the first writes, the others
 // add, in LDS).  The tiles of one channel range follow each other on one XCD.
 //
-// It is bound by the matrix pipe and the vector instructions that expand the
-// spike bits, which share the issue slots: 6144 -> 1536 at 2500 rows 29.2 us
+// No unit bounds it alone: at 2500 rows of 6144 -> 1536 the matrix units are busy
+// 33% of the launch and the vector ALU, which expands the spike bits, 39%; the two
+// waves of a SIMD overlap them only in part, and 6.5 us are launch, staging and
+// sums.  Measured as a chain of dependent calls: 6144 -> 1536 at 2500 rows 29.2 us
 // (1.6 POPS) against 43.1 in 64 x 48 tiles, 27.0 with the bits not expanded in a
 // timing copy; 1536 -> 1536 13.5 against 24.8, 4096 -> 4096 at 1300 rows 38.9
 // against 62.4, 512 -> 4096 at 2500 rows 24.8 against 36.9.  With 16x16x64
