@@ -233,7 +233,13 @@ void launch_stream_t(const spike_stream* s, int n_tiles, unsigned units, const u
 // MiB) 12 / 13 / 19 / 24 / 30 against 8 / 11 / 16 / 28 / 50; 768 wide, 10 blocks (28
 // MiB) 8 / 10 / 11 / 15 / 18 against 6 / 10 / 15 / 25 / 46; 256 wide, 4 blocks 6.6 / 7.4 /
 // 7.4 / 7.3 / 7.3 against 4.4 / 5.7 / 7.5 / 11 / 18.  The host cannot know the rate; the
-// lines lie where a decoder's usual rates (about 0.1) break even.
+// lines lie where a decoder's rates (0.05 to 0.20 over its blocks) break even.
+// Launches of few tiles break even later than others, a workgroup reading its 128
+// channels at 3.6 ns a column whatever the chip has free: 9 tokens, 4 blocks of 1536
+// (96 tiles), 0.05 / 0.10 / 0.20 and 0.05 to 0.20 over the blocks, 16 / 24 / 30 and 28
+// us against 11 / 17 / 30 and 28; 4 blocks of 512 (32 tiles) 9.4 / 11.4 / 11.1 and 11.4
+// against 6.4 / 8.7 / 13.0 and 12.8; 4 projections of 16384 -> 512, 16 tokens, 45 / 62 /
+// 64 and 61 against 19 / 34 / 64 and 63, at 0.4 about 65 against 125.
 constexpr int kStreamMatMinRows = 9, kStreamMatSmallMinRows = 5;
 constexpr int64_t kStreamMatSmallBytes = 128ll << 20;
 // Weights that are read once and do not fit the 256 MB Infinity Cache are
