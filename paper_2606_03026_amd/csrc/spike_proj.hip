@@ -239,7 +239,8 @@ void launch_stream_t(const spike_stream* s, int n_tiles, unsigned units, const u
 // (96 tiles), 0.05 / 0.10 / 0.20 and 0.05 to 0.20 over the blocks, 16 / 24 / 30 and 28
 // us against 11 / 17 / 30 and 28; 4 blocks of 512 (32 tiles) 9.4 / 11.4 / 11.1 and 11.4
 // against 6.4 / 8.7 / 13.0 and 12.8; 4 projections of 16384 -> 512, 16 tokens, 45 / 62 /
-// 64 and 61 against 19 / 34 / 64 and 63, at 0.4 about 65 against 125.
+// 64 and 61 against 19 / 34 / 64 and 63; one of 16384 beside 20 of 1024, 1024
+// channels, 17 tokens, 0.02 / 0.1 / 0.4, 26 / 64 / 70 against 11 / 37 / 132.
 constexpr int kStreamMatMinRows = 9, kStreamMatSmallMinRows = 5;
 constexpr int64_t kStreamMatSmallBytes = 128ll << 20;
 // Weights that are read once and do not fit the 256 MB Infinity Cache are
