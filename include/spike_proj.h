@@ -269,8 +269,9 @@ int spike_stack_forward_fused(const spike_proj_t *projs, int32_t n_proj, const u
  * tokens, each running n_proj projections, all in one launch.  projs holds
  * n_sets * n_proj handles; token t uses projs[(t % n_sets) * n_proj + j]
  * (n_sets > 1 rotates address-distinct weight copies).  All handles must
- * share N; 1 <= n_proj <= 64 and every K <= 16384.  Per token, masks hold the projections' rows back to back
- * (token stride sum_j ceil(K_j/64) words) and out holds n_proj * N floats.
+ * share N; 1 <= n_proj <= 64 and every K <= 16384.  Per token, masks hold the
+ * projections' rows back to back (token stride sum_j ceil(K_j/64) words) and out
+ * holds n_proj * N floats.
  * create() copies a small descriptor table to the device (allocates);
  * forward() only launches.  The tokens of one weight copy are independent
  * rows: where 9 or more share a copy (5 where the weights of all copies take up
